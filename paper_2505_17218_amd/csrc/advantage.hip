@@ -239,62 +239,136 @@ live_compact_k(const int32_t* __restrict__ tok, const int32_t* __restrict__ slot
     if (threadIdx.x == 0) *count = base;
 }
 
-// Loss over the kept samples, float64, reproducible bit for bit.  Each thread takes
-// kept samples k, k + 256, ... and sums a sample's per-token values in token order;
-// the 256 partials are then added as a pairwise tree.  Surrogate: A S (PG, no old log-probs) or PPO's
-// min(rho A, clip(rho, 1 - eps, 1 + eps) A) with rho = exp(S - S_old); the KL sums
-// (if given) enter with weight beta.  stats[4 n ..] = (S, S_old, KL, dloss/dS).
-__global__ void __launch_bounds__(kThreads)
-policy_loss_k(const float* __restrict__ lp, const float* __restrict__ lp_old, const float* __restrict__ kl, int64_t ld,
-              int T, const int32_t* __restrict__ len, const float* __restrict__ adv,
-              const int32_t* __restrict__ kept, const int32_t* __restrict__ kept_count, int n_total, double clip_eps,
-              double beta, double* __restrict__ loss, double* __restrict__ seq_lp, double* __restrict__ stats) {
-    __shared__ double buf[kThreads], kbuf[kThreads];
-    const int K = *kept_count;
-    const double N = (double)n_total;
-    double acc = 0.0, kacc = 0.0;
-    for (int k = threadIdx.x; k < K; k += kThreads) {
-        const int n = kept[k];
-        const int L = len ? min(max(len[n], 0), T) : T;
-        const float* row = lp + (int64_t)n * ld;
-        double S = 0.0;
-        for (int t = 0; t < L; ++t) S += (double)row[t];
-        double S_old = S, Kn = 0.0;
-        if (lp_old) {
-            const float* ro = lp_old + (int64_t)n * ld;
-            S_old = 0.0;
-            for (int t = 0; t < L; ++t) S_old += (double)ro[t];
-        }
-        if (kl) {
-            const float* rk = kl + (int64_t)n * ld;
-            for (int t = 0; t < L; ++t) Kn += (double)rk[t];
-        }
-        const double A = (double)adv[n];
-        double sur, w;
-        if (!lp_old) {
-            sur = A * S;
-            w = -A / N;
-        } else {
-            const double rho = exp(S - S_old);
-            const double un = rho * A;
-            const double cl = fmin(fmax(rho, 1.0 - clip_eps), 1.0 + clip_eps) * A;
-            sur = fmin(un, cl);
-            w = un <= cl ? -A * rho / N : 0.0;
-        }
-        if (seq_lp) seq_lp[n] = S;
-        if (stats) {
-            stats[4 * (int64_t)n + 0] = S;
-            stats[4 * (int64_t)n + 1] = S_old;
-            stats[4 * (int64_t)n + 2] = Kn;
-            stats[4 * (int64_t)n + 3] = w;
-        }
-        acc += sur;
-        kacc += Kn;
+// Loss over the kept samples, float64, reproducible bit for bit.  A wave sums a sample's
+// per-token values (loss_row_sum: lanes over tokens, then the lanes by an xor tree); the
+// samples' terms are then added by one workgroup, thread t taking kept samples t, t + 1024,
+// ... in order and the threads as a pairwise tree.  Surrogate: A S (PG, no old log-probs)
+// or PPO's min(rho A, clip(rho, 1 - eps, 1 + eps) A) with rho = exp(S - S_old); the KL
+// sums (if given) enter with weight beta.  stats[4 n ..] = (S, S_old, KL, dloss/dS).
+//
+// The rows are what there is to read (12 MB for 1024 samples of 1024 tokens), so they are
+// read by a launch of their own, a wave per sample over the whole GPU, which leaves the
+// sums in the caller's stats (or seq_lp) for the one-workgroup sum.  One thread per sample
+// in a single workgroup took 560 us at 1024 x 1024 (three rows, 614 kept, mean length
+// 512): uncoalesced 4-byte reads and a serial chain of adds on one CU; the two launches
+// take under 10 us (the call 593 -> 24 us, most of it the host).  Without either output the one workgroup's waves read the rows too.
+struct LossArgs {
+    const float *lp, *lp_old, *kl;
+    int64_t ld;
+    int T;
+    const int32_t* len;
+    const float* adv;
+    const int32_t *kept, *kept_count;
+    int n_total;
+    double clip_eps, beta;
+    double *loss, *seq_lp, *stats;
+};
+
+// Sum of row[0 .. L-1] over the wave, the same value in every lane.
+DASH_DEV double loss_row_sum(const float* __restrict__ row, int L) {
+    const int lane = threadIdx.x & 63;
+    double acc = 0.0;
+    int t = lane;
+    for (; t + 7 * 64 < L; t += 8 * 64) {  // eight loads in flight per lane
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = row[t + 64 * j];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc += (double)v[j];
     }
-    buf[threadIdx.x] = acc;
-    kbuf[threadIdx.x] = kacc;
-    __syncthreads();
+    for (; t < L; t += 64) acc += (double)row[t];
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) acc += __shfl_xor(acc, o, 64);
+    return acc;
+}
+
+struct LossRow {
+    double S, S_old, kl;
+};
+
+DASH_DEV LossRow loss_row(const LossArgs& a, int n) {
+    const int L = a.len ? min(max(a.len[n], 0), a.T) : a.T;
+    LossRow r;
+    r.S = loss_row_sum(a.lp + (int64_t)n * a.ld, L);
+    r.S_old = a.lp_old ? loss_row_sum(a.lp_old + (int64_t)n * a.ld, L) : r.S;
+    r.kl = a.kl ? loss_row_sum(a.kl + (int64_t)n * a.ld, L) : 0.0;
+    return r;
+}
+
+// The sample's surrogate and the loss's derivative with respect to S.
+DASH_DEV double loss_surrogate(const LossArgs& a, const LossRow& r, double A, double& w) {
+    const double N = (double)a.n_total;
+    if (!a.lp_old) {
+        w = -A / N;
+        return A * r.S;
+    }
+    const double rho = exp(r.S - r.S_old);
+    const double un = rho * A;
+    const double cl = fmin(fmax(rho, 1.0 - a.clip_eps), 1.0 + a.clip_eps) * A;
+    w = un <= cl ? -A * rho / N : 0.0;
+    return fmin(un, cl);
+}
+
+constexpr int kLossRowWaves = 4;  // samples per workgroup of the row launch
+
+__global__ void __launch_bounds__(64 * kLossRowWaves) loss_rows_k(LossArgs a) {
+    const int K = *a.kept_count;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int k = blockIdx.x * kLossRowWaves + wave; k < K; k += gridDim.x * kLossRowWaves) {
+        const int n = a.kept[k];
+        const LossRow r = loss_row(a, n);
+        if ((threadIdx.x & 63) == 0) {
+            if (a.seq_lp) a.seq_lp[n] = r.S;
+            if (a.stats) {
+                double w;
+                loss_surrogate(a, r, (double)a.adv[n], w);
+                double* st = a.stats + 4 * (int64_t)n;
+                st[0] = r.S;
+                st[1] = r.S_old;
+                st[2] = r.kl;
+                st[3] = w;
+            }
+        }
+    }
+}
+
+// FROM: where the samples' sums come from: 0 read here, 1 from stats, 2 from seq_lp (S alone).
+template <int FROM>
+__global__ void __launch_bounds__(kThreads) loss_sum_k(LossArgs a) {
+    __shared__ double buf[kThreads], kbuf[kThreads];
+    __shared__ LossRow rows[FROM == 0 ? kThreads : 1];
+    const int K = *a.kept_count;
     const int tid = threadIdx.x;
+    const double N = (double)a.n_total;
+    double acc = 0.0, kacc = 0.0;
+    for (int k0 = 0; k0 < K; k0 += kThreads) {
+        if constexpr (FROM == 0) {
+            for (int i = tid >> 6; i < min(kThreads, K - k0); i += kWaves) {
+                const LossRow r = loss_row(a, a.kept[k0 + i]);
+                if ((tid & 63) == 0) rows[i] = r;
+            }
+            __syncthreads();
+        }
+        if (k0 + tid < K) {
+            const int n = a.kept[k0 + tid];
+            LossRow r;
+            if constexpr (FROM == 0) {
+                r = rows[tid];
+            } else if constexpr (FROM == 1) {
+                const double* st = a.stats + 4 * (int64_t)n;
+                r = LossRow{st[0], st[1], st[2]};
+            } else {
+                r = LossRow{a.seq_lp[n], 0.0, 0.0};
+            }
+            double w;
+            acc += loss_surrogate(a, r, (double)a.adv[n], w);
+            kacc += r.kl;
+        }
+        if constexpr (FROM == 0) __syncthreads();  // rows are refilled next
+    }
+    buf[tid] = acc;
+    kbuf[tid] = kacc;
+    __syncthreads();
     for (int half = kThreads >> 1; half >= 1; half >>= 1) {
         double x = 0.0, y = 0.0;
         if (tid < half) {
@@ -308,10 +382,10 @@ policy_loss_k(const float* __restrict__ lp, const float* __restrict__ lp_old, co
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         double l = -buf[0] / N;
-        if (kl) l += beta * kbuf[0] / N;
-        *loss = l;
+        if (a.kl) l += a.beta * kbuf[0] / N;
+        *a.loss = l;
     }
 }
 
@@ -321,8 +395,19 @@ hipError_t launch_policy_loss(const float* lp, const float* lp_old, const float*
                               const int32_t* len, const float* adv, const int32_t* kept, const int32_t* kept_count,
                               int n_total, double clip_eps, double beta, double* loss, double* seq_lp, double* stats,
                               hipStream_t st) {
-    policy_loss_k<<<1, kThreads, 0, st>>>(lp, lp_old, kl, ld, T, len, adv, kept, kept_count, n_total, clip_eps, beta,
-                                          loss, seq_lp, stats);
+    const LossArgs a{lp, lp_old, kl, ld, T, len, adv, kept, kept_count, n_total, clip_eps, beta, loss, seq_lp, stats};
+    // the sums' way from the row launch to the final one: stats, or seq_lp where S is all there is
+    const int from = stats ? 1 : seq_lp && !lp_old && !kl ? 2 : 0;
+    if (from || seq_lp) {
+        const int blocks = n_total / kLossRowWaves < 2048 ? n_total / kLossRowWaves + 1 : 2048;
+        loss_rows_k<<<blocks, 64 * kLossRowWaves, 0, st>>>(a);
+    }
+    if (from == 1)
+        loss_sum_k<1><<<1, kThreads, 0, st>>>(a);
+    else if (from == 2)
+        loss_sum_k<2><<<1, kThreads, 0, st>>>(a);
+    else
+        loss_sum_k<0><<<1, kThreads, 0, st>>>(a);
     return hipGetLastError();
 }
 

@@ -190,7 +190,7 @@ def pg_loss(logprobs: torch.Tensor, adv: torch.Tensor, kept: torch.Tensor, lengt
     """dash_pg_loss over the kept indices: returns (float64 loss [1], float64 sequence log-probs [N])."""
     N, T = logprobs.shape
     dev = logprobs.device
-    cnt = torch.tensor([kept.numel()], dtype=torch.int32, device=dev)
+    cnt = torch.full((1,), kept.numel(), dtype=torch.int32, device=dev)
     loss = torch.empty(1, dtype=torch.float64, device=dev)
     seq = torch.zeros(N, dtype=torch.float64, device=dev)
     kept_buf = kept if kept.numel() else torch.zeros(1, dtype=torch.int32, device=dev)
@@ -209,7 +209,7 @@ def policy_loss(logprobs: torch.Tensor, adv: torch.Tensor, kept: torch.Tensor, l
     for t in (logprobs_old, kl):
         if t is not None and (t.shape != logprobs.shape or t.stride() != logprobs.stride()):
             raise ValueError("logprobs_old and kl must have the logprobs' shape and strides")
-    cnt = torch.tensor([kept.numel()], dtype=torch.int32, device=dev)
+    cnt = torch.full((1,), kept.numel(), dtype=torch.int32, device=dev)
     loss = torch.empty(1, dtype=torch.float64, device=dev)
     stats = torch.zeros(N, 4, dtype=torch.float64, device=dev)
     kept_buf = kept if kept.numel() else torch.zeros(1, dtype=torch.int32, device=dev)

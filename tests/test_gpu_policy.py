@@ -215,3 +215,27 @@ def test_policy_loss_edge_cases():
     loss, _ = engine.policy_loss(lp4, torch.tensor([1.0, 1.0, -1.0, -2.0], device="cuda"), dev_i32([0, 1, 2, 3]),
                                  logprobs_old=old4, clip_eps=0.25)
     assert abs(float(loss.item()) - 0.3125) < 1e-6
+
+
+@pytest.mark.parametrize("N,T", [(3, 1), (1500, 513)])
+def test_loss_routes_bit_identical(N, T):
+    """The row sums go through stats, through the sequence log-probs, or stay inside the one
+    workgroup (neither output given): the same loss bit for bit, past 1024 kept samples too."""
+    lp, lp_old, kl, lengths, adv, _ = _loss_inputs(N + (-N) % 8, T, 61)
+    kept = np.flatnonzero(np.arange(N) % 7 != 3).astype(np.int32)
+    d = [torch.from_numpy(np.ascontiguousarray(v[:N])).cuda() for v in (lp, lp_old, kl, lengths, adv)]
+    d_kept, cnt = dev_i32(kept), dev_i32([kept.size])
+    loss = torch.empty(4, dtype=torch.float64, device="cuda")
+    stats = torch.zeros(N, 4, dtype=torch.float64, device="cuda")
+    seq = torch.zeros(N, dtype=torch.float64, device="cuda")
+    common = (d[0].stride(0), T, d[3].data_ptr(), d[4].data_ptr(), d_kept.data_ptr(), cnt.data_ptr(), N)
+    for i, out in enumerate((stats.data_ptr(), None)):
+        L.dash_policy_loss(d[0].data_ptr(), d[1].data_ptr(), d[2].data_ptr(), *common, 0.2, 0.04,
+                           loss[i:].data_ptr(), out, engine.stream_handle())
+    for i, out in enumerate((seq.data_ptr(), None)):
+        L.dash_pg_loss(d[0].data_ptr(), *common, loss[2 + i:].data_ptr(), out, engine.stream_handle())
+    got = loss.cpu().numpy()
+    want, _ = opol.policy_loss(lp[:N], adv[:N], kept, lengths[:N], lp_old=lp_old[:N], kl=kl[:N], clip_eps=0.2, beta=0.04)
+    assert abs(got[0] - want) <= 1e-12 * max(1.0, abs(want))
+    assert got[0] == got[1] and got[2] == got[3]
+    np.testing.assert_array_equal(seq.cpu().numpy(), stats.cpu().numpy()[:, 0])
