@@ -9,18 +9,25 @@
 // -ffp-contract=off: see sampler_math.h.
 //
 // Screening.  The exact noise -ln(-ln u) (two correctly rounded divisions) is
-// the expensive part, so every entry is first scored with a cheap noise from the
+// the expensive part, so an entry is first scored with a cheap noise from the
 // hardware logarithm, whose distance to the exact noise is below kScreenTol for
 // every value u can take (checked exhaustively by dash_sampler_check).  With the
 // fp32 rounding of the sums added, each entry's exact score lies within a margin
-// of its cheap score.  The wave keeps a shared lower bound on the best exact
+// of its cheap score.  The workgroup keeps in LDS a lower bound on the best exact
 // score seen so far (exact scores of evaluated entries, cheap score minus margin
 // of the rest); an entry whose cheap score plus margin falls below it cannot be
 // the argmax and is skipped, every other entry gets its exact score.  The winner
 // is therefore always evaluated exactly: tokens are bit-identical to scoring
 // every entry exactly.  Before the cheap noise, an upper bound on the exact noise
-// read off the random word's leading ones (noise_bound) already rules out almost
-// every entry once the bound has risen, without any logarithm.
+// read off the random word's leading ones (noise_bound) rules out almost every
+// entry once the bound has risen, without any logarithm, and before that one
+// bound for a group of four (largest score, largest word) rules out whole groups.
+//
+// What bounds it: vector instructions, about half of them Philox (20 quarter-rate
+// 64-bit multiplies per group).  1024 x 151,936 at temperature 1: 127.7 us (4.9 TB/s of
+// logits), against 173.8 us with a bound per wave (every group then refreshed it with a
+// wave-wide maximum, and sixteen waves each raised their own), a bound test per entry, an
+// online sum with a select per entry and two-operand xors in Philox.
 #include <cstring>
 
 #include "common.h"
@@ -42,16 +49,24 @@ constexpr float kScreenTol = 1.6e-5f;
 
 DASH_DEV bool better(float s, int i, float bs, int bi) { return s > bs || (s == bs && i < bi); }
 
-// One entry x into an online (max mx, sum z of e^(v - mx)): a new maximum rescales the
-// sum (z e^(mx - x) + 1), any other entry adds e^(x - mx).  Both cases are one
-// exponential of -|x - mx| (x - mx and mx - x are exact negations), chosen without a
-// branch; the sampler and the log-prob gather share it, so they sum in the same way.
-DASH_DEV void lse_push(float& mx, float& z, float x) {
-    const float d = x - mx;  // +inf while mx is -inf
-    const float e = __expf(-fabsf(d));
-    const bool up = d > 0.f;
-    z = up ? z * e + 1.0f : z + e;
-    mx = up ? x : mx;
+// Four entries into an online (max mx, sum z of e^(v - mx)): one rescale of the sum to the
+// new maximum, then the four terms, added in pairs.  Non-finite entries are skipped.  The
+// sampler and the log-prob gather share it, so they sum in the same way.  A sum of the
+// four that is finite shows that all four are (an overflowing sum only takes the longer
+// way); waves without a non-finite entry skip the per-entry masks.
+DASH_DEV void lse_push4(float& mx, float& z, const float (&x)[4]) {
+    float v[4] = {x[0], x[1], x[2], x[3]};
+    const float s = (v[0] + v[1]) + (v[2] + v[3]);
+    if (__any(!(fabsf(s) < INFINITY))) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = fabsf(v[j]) < INFINITY ? v[j] : -INFINITY;
+    }
+    const float m = fmaxf(mx, fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
+    const float ref = m == -INFINITY ? 0.f : m;  // nothing finite yet: every term is e^-inf = 0
+    const float a = __expf(mx - ref);
+    const float e0 = __expf(v[0] - ref), e1 = __expf(v[1] - ref), e2 = __expf(v[2] - ref), e3 = __expf(v[3] - ref);
+    z = z * a + ((e0 + e1) + (e2 + e3));
+    mx = m;
 }
 
 // Non-temporal (streaming) vector load, for logits read once.
@@ -163,46 +178,65 @@ sample_k(const float* __restrict__ logits, int64_t ld, int vocab, const int32_t*
     __shared__ int red_i[kThreads / 64];
     __shared__ float red_m[kThreads / 64];
     __shared__ float red_z[kThreads / 64];
+    __shared__ float floor_s;  // lower bound on the best exact score the workgroup has seen
     const int b = blockIdx.x;
     const int r = row_of ? row_of[b] : b;
     const float* row = logits + (int64_t)r * ld;
     const uint32_t u_id = (uint32_t)uid[b], st = (uint32_t)step[b];
+    if (threadIdx.x == 0) floor_s = -INFINITY;
+    __syncthreads();
 
     float best_s = -INFINITY;
     int best_i = 0x7FFFFFFF;
     float mx = -INFINITY, z = 0.f;
-    float floor_w = -INFINITY;  // wave-shared lower bound on the best exact score seen
     const int n4 = (vocab + 3) >> 2;
-    // every lane of the wave runs the same number of iterations (the shared bound needs all
-    // lanes); the loop counter lives in a scalar register, so its branches are uniform
+    // every lane of the wave runs the same number of iterations; the loop counter lives in a
+    // scalar register, so its branches are uniform
     const int lane0 = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63);
     const __amdgpu_buffer_rsrc_t rs = row_rsrc(row, vocab);
-    // Scores one group of four entries of this lane (g = its group) and refreshes the
-    // wave's shared bound.
-    auto score4 = [&](float (&l)[4], int g) {
-        vocab_mask(l, g, vocab);
-        float floor_t = floor_w;
-        if (g < n4) {
-            // the round keys are derived here rather than kept: precomputed they held 20
-            // scalar registers through the loop
-            uint32_t kk0 = k0, kk1 = k1;
-            asm volatile("" : "+s"(kk0), "+s"(kk1));
-            const U4 x = philox4x32_10(U4{(uint32_t)g, st, u_id, 0u}, kk0, kk1);
+    const float inv_t = UNIT_T ? 1.f : div_rn(1.f, temperature);
+    // Scores one group of four entries of this lane (g = its group, gw the wave's first) and
+    // raises the shared bound.
+    auto score4 = [&](float (&l)[4], int g, int gw) {
+        if (4 * (gw + 64) > vocab) vocab_mask(l, g, vocab);  // the wave's last group (uniform)
+        // Read ahead of the noise, so that the noise hides the LDS latency.  A stale bound is
+        // a lower one: more entries are evaluated, the result is the same.
+        const float floor_w = __hip_atomic_load(&floor_s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        // the round keys are derived here rather than kept: precomputed they held 20
+        // scalar registers through the loop
+        uint32_t kk0 = k0, kk1 = k1;
+        asm volatile("" : "+s"(kk0), "+s"(kk1));
+        const U4 x = philox4x32_10(U4{(uint32_t)g, st, u_id, 0u}, kk0, kk1);
+        float sc[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if constexpr (UNIT_T) {
+                sc[j] = l[j];
+            } else {
+                // l / T by a product and one corrected step (within the margin of the exact
+                // quotient, which the candidates below get; non-finite values stay non-finite)
+                const float q = l[j] * inv_t;
+                sc[j] = __builtin_fmaf(__builtin_fmaf(-q, temperature, l[j]), inv_t, q);
+            }
+        }
+        // No entry of the group can reach the bound, even with the group's largest noise:
+        // true for almost every group once the bound has risen.  (The maxima pass over NaN
+        // entries, which can win nothing; infinities fail the comparison.)
+        const float m4 = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
+        const float hi4 = m4 + noise_bound(max(max(x.x, x.y), max(x.z, x.w)));
+        if (__any(!(hi4 + screen_margin(hi4) < floor_w))) {
             const uint32_t xs[4] = {x.x, x.y, x.z, x.w};
+            float floor_t = floor_w;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 if (!isfinite(l[j])) continue;
-                const float sc = UNIT_T ? l[j] : div_rn(l[j], temperature);
                 // even the largest noise this word allows cannot reach the bound: skip the logs
-                const float hi = sc + noise_bound(xs[j]);
-                if (hi + screen_margin(hi) < floor_t) {
-                    lse_push(mx, z, sc);
-                    continue;
-                }
-                const float sa = sc + cheap_gumbel(xs[j]);
+                const float hi = sc[j] + noise_bound(xs[j]);
+                if (hi + screen_margin(hi) < floor_t) continue;
+                const float sa = sc[j] + cheap_gumbel(xs[j]);
                 const float mg = screen_margin(sa);
-                if (sa + mg >= floor_t) {
-                    const float s = sc + gumbel_from_bits(xs[j]);  // exact
+                if (!(sa + mg < floor_t)) {
+                    const float s = (UNIT_T ? l[j] : div_rn(l[j], temperature)) + gumbel_from_bits(xs[j]);  // exact
                     if (s > best_s) {  // indices grow within a thread: strict > keeps the smallest on ties
                         best_s = s;
                         best_i = 4 * g + j;
@@ -211,10 +245,12 @@ sample_k(const float* __restrict__ logits, int64_t ld, int vocab, const int32_t*
                 } else {
                     floor_t = fmaxf(floor_t, sa - mg);
                 }
-                lse_push(mx, z, sc);
             }
+            const float f = wave_max_f(floor_t);
+            if (f > floor_w && (threadIdx.x & 63) == 0)
+                (void)__hip_atomic_fetch_max(&floor_s, f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        floor_w = wave_max_f(floor_t);
+        lse_push4(mx, z, sc);
     };
     // Two groups in flight per lane, in two register sets that take turns: a set is
     // copied out right after the other set's load has been issued (so the wait before the
@@ -232,12 +268,12 @@ sample_k(const float* __restrict__ logits, int64_t ld, int vocab, const int32_t*
         fetch_raw4<VEC4>(rs, threadIdx.x + 2 * kThreads, set_a);
         for (int g0 = lane0; g0 < n4; g0 += 2 * kThreads) {
             const int g = g0 + (threadIdx.x & 63);
-            score4(l, g);
+            score4(l, g, g0);
             if (g0 + kThreads >= n4) break;  // wave-uniform
 #pragma unroll
             for (int j = 0; j < 4; ++j) l[j] = copy_out(set_b[j]);
             fetch_raw4<VEC4>(rs, g + 3 * kThreads, set_b);
-            score4(l, g + kThreads);
+            score4(l, g + kThreads, g0 + kThreads);
 #pragma unroll
             for (int j = 0; j < 4; ++j) l[j] = copy_out(set_a[j]);
             fetch_raw4<VEC4>(rs, g + 4 * kThreads, set_a);
@@ -332,11 +368,7 @@ logprob_gather_k(const float* __restrict__ logits, int64_t ld, int vocab, const 
     for (int g = threadIdx.x; g < n4; g += kThreads) {
         float l[4] = {nxt[0], nxt[1], nxt[2], nxt[3]};
         fetch4(row, g + kThreads, n4, vocab, vec4, nxt);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (!isfinite(l[j])) continue;
-            lse_push(mx, z, l[j]);
-        }
+        lse_push4(mx, z, l);
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {

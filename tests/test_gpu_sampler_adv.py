@@ -120,6 +120,27 @@ def test_sample_row_layouts(V, ld, off):
     np.testing.assert_array_equal(lp2.cpu().numpy().view(np.uint32), lps.cpu().numpy().view(np.uint32))
 
 
+@pytest.mark.parametrize("temp", [1.0, 0.7, 1e-3])
+@pytest.mark.parametrize("V", [3, 255, 256, 4097, 8196])
+def test_sample_masked_rows_and_group_edges(V, temp):
+    """Vocabularies around a thread's group of four, a wave's 256 entries and a second and
+    third pass of the workgroup, with most entries masked (-inf), some NaN or +inf: groups
+    that mix them with finite entries, and temperatures on both sides of the division."""
+    R = 8
+    rng = np.random.default_rng(V)
+    logits = synth.make_logits(R, V, seed=V, scale=3.0)
+    logits[rng.random((R, V)) < 0.7] = -np.inf
+    logits[rng.random((R, V)) < 0.05] = np.nan
+    logits[rng.random((R, V)) < 0.02] = np.inf
+    logits[:, V - 1] = 0.5  # a finite last entry in every row
+    uid, step = np.arange(R, dtype=np.int32), np.full(R, 2, np.int32)
+    toks, lps = engine.sample(torch.from_numpy(logits).cuda(), dev_i32(uid), dev_i32(step), temp, 8)
+    want_t, want_lp = osm.sample(logits, uid, step, temp, 8)
+    np.testing.assert_array_equal(toks.cpu().numpy(), want_t)
+    # float32 scores l / T: a log-prob moves by their rounding as well
+    np.testing.assert_allclose(lps.cpu().numpy(), want_lp, atol=LP_ATOL + 2.0 ** -22 * 15.0 / temp, rtol=LP_RTOL)
+
+
 def test_sample_deterministic_and_independent_of_batch_position():
     logits = synth.make_logits(8, 151936, seed=5)
     uid = np.arange(8, dtype=np.int32)
