@@ -595,6 +595,354 @@ gemm_lds_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __r
     }
 }
 
+// ---- wide tiles ---------------------------------------------------------------
+// The large-batch kernel (prefill, teacher forcing, wide decode batches): WGM x WGN waves of
+// TM x TN 32 x 32 blocks, operands direct to LDS in two stages of 64-deep tiles, fragments
+// double-buffered in registers.  A k-step is four clusters of TM x TN MFMAs; each cluster
+// multiplies one 16-deep slice while the next slice's fragments are read, and the stage
+// barrier sits before the last cluster: by then every wave has read all of the step's stage
+// (its last fragments are in registers) and its own part of the next stage has landed, so
+// the last cluster runs beside the first fragment reads of the next stage and the loads of
+// step k + 2 into the stage just finished.  The instruction mix of every cluster is pinned
+// (one MFMA, one LDS read, one load, ...): left to itself the compiler bunches the reads
+// (3-5% slower).
+//
+// Eight waves of 128 x 64 on a 256 x 256 tile: each fragment feeds four (two) MFMAs, so LDS
+// reads take ~770 cycles of the 2060 MFMA cycles of a step; two waves per SIMD fill each
+// other's barrier waits (four waves of 128 x 128, one per SIMD, 1-8% slower; sixteen waves
+// of 64 x 64 with register-staged operands, the earlier kernel, 10-20% slower).  At 4096 x
+// 4096 x 12288 it runs at 1353 TFLOP/s with the MFMA pipes 73% busy and the clock down to
+// 1.8 GHz: the power limit, not the pipe, is next.  What a shape loses beyond that is per
+// tile (load latency before the first step, the output after the last).  Stages of 32-deep
+// half lines (four or five of them in flight) were 5-10% slower, and touching the lines of
+// later steps (one dword per 64 bytes) 6-12%: the vector memory path, 64 bytes a cycle
+// and CU, is half busy already, so requests cost more than the latency they would hide.
+// Same fragments and MFMA order as the other kernels: identical bits.
+
+// Tile order: blocks of gm tile rows, column by column inside a block, so that the ~32
+// tiles an XCD works on at a time span a near-square patch and share operand lines in its
+// L2 (rows fastest over all of M re-read the left operand from beyond L2 for every column:
+// gate/up at 16384 rows 847 us against 701-737 us with 4-6 rows a block).
+DASH_DEV void wide_tile_of(int w, int m_tiles, int n_tiles, int gm, int& mt, int& nt) {
+    const int per = gm * n_tiles, g = w / per, r = w - g * per;
+    const int rows = min(gm, m_tiles - g * gm);
+    mt = g * gm + r % rows;
+    nt = r / rows;
+}
+
+// Cache page and key of every tile row (QKV epilogue), and per 32-row block whether its
+// rows are 32 consecutive keys of one page starting at a multiple of 32 (prefill of whole
+// pages): their V values then form whole 16-byte groups.
+template <int BM>
+struct WideQkvRows {
+    int page[BM], key[BM], run[BM / 32];
+};
+
+template <int BM>
+DASH_DEV void wide_qkv_rows(const QkvRopeArgs& qa, int M, int m0, int tid, WideQkvRows<BM>& rows) {
+    if (tid >= BM) return;
+    const int m = m0 + tid;
+    int page = -1, key = -1;
+    if (m < M) {
+        const int p = qa.pos[m];
+        page = kv_page_of(qa.g, qa.page_table, qa.slot[m], p);
+        key = p % qa.g.page_size;
+        if (page < 0 && qa.status) atomicOr(qa.status, 1u);
+    }
+    rows.page[tid] = page;
+    rows.key[tid] = key;
+    const int lane = tid & 63, first = lane & 32;
+    const int page0 = __shfl(page, first, 64), key0 = __shfl(key, first, 64);
+    const bool in_run = page >= 0 && page == page0 && key0 % 32 == 0 && key == key0 + (lane & 31);
+    const uint64_t all = __ballot(in_run);
+    if ((lane & 31) == 0) rows.run[tid >> 5] = (uint32_t)(all >> first) == 0xFFFFFFFFu;
+}
+
+// Bias, RoPE and the KV append straight from the accumulators: a wave's 128 columns are
+// whole heads, and the two halves of a RoPE pair sit in the same lane and register of
+// column blocks two (head dim 128) or one (64) apart.  Rotated q and k leave through LDS of
+// the wave's own (hs: 32 rows of kQkvRow elements), 16 bytes a lane: q rows are contiguous,
+// and so are 8 dims of a key in the K block.  (With 2-byte stores per element the 1.5B
+// projection of 16,384 rows took 117 us instead of 90.)
+constexpr int kQkvRow = 128 + 8;
+
+template <int BM, int WM, int TM>
+DASH_DEV void wide_qkv_epilogue(const f32x16_t (&acc)[TM][4], const QkvRopeArgs& qa, int M, int N, int m0, int n0,
+                                int wr, int lane, const WideQkvRows<BM>& rows, bf16_t* hs) {
+    const KVGeom& g = qa.g;
+    const int hd = g.head_dim, half = hd >> 1, lg_hd = hd == 128 ? 7 : 6;
+    const int col = lane & 31, rbase = (lane >> 5) * 4;
+    const int q_cols = qa.n_heads * hd, k_end = q_cols + g.n_kv * hd;
+    if (n0 >= N) return;
+    float bias[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bias[j] = bf2f(qa.bias[n0 + j * 32 + col]);
+    if (n0 < k_end) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int b0 = wr * WM + i * 32;  // first tile row of the block
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const int d = hd == 128 ? p * 32 + col : col;         // pair (d, d + half) of the head
+                bf16_t* hp = hs + (hd == 128 ? d : p * 64 + d);       // its column among the wave's 128
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int rr = (r >> 2) * 8 + rbase + (r & 3);
+                    const size_t m = min(m0 + b0 + rr, M - 1);
+                    const float2 cs = *reinterpret_cast<const float2*>(qa.cs + (m * half + d) * 2);
+                    const float a = hd == 128 ? acc[i][p][r] + bias[p] : acc[i][2 * p][r] + bias[2 * p];
+                    const float b = hd == 128 ? acc[i][p + 2][r] + bias[p + 2] : acc[i][2 * p + 1][r] + bias[2 * p + 1];
+                    float lo, hi;
+                    rope_pair(a, b, cs.x, cs.y, lo, hi);
+                    hp[rr * kQkvRow] = f2bf(lo);
+                    hp[rr * kQkvRow + half] = f2bf(hi);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int rr = u * 4 + (lane >> 4), c8 = (lane & 15) * 8, m = m0 + b0 + rr;
+                if (m >= M) continue;
+                const uint4 v = *reinterpret_cast<const uint4*>(hs + rr * kQkvRow + c8);
+                if (n0 < q_cols) {
+                    *reinterpret_cast<uint4*>(qa.q_out + (size_t)m * q_cols + n0 + c8) = v;
+                } else if (rows.page[b0 + rr] >= 0) {
+                    const int jj = n0 + c8 - q_cols;
+                    bf16_t* kb = qa.pool + kv_block(g, qa.layer, rows.page[b0 + rr], jj >> lg_hd, 0);
+                    *reinterpret_cast<uint4*>(kb + k_index_bf16(g, rows.key[b0 + rr], jj & (hd - 1))) = v;
+                }
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int b0 = wr * WM + i * 32;
+        if (rows.run[b0 >> 5]) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int jj = n0 + j * 32 + col - k_end;
+                bf16_t* vb = qa.pool + kv_block(g, qa.layer, rows.page[b0], jj >> lg_hd, 1) +
+                             ((size_t)((rows.key[b0] >> 5) * 4 + (lane >> 5)) * hd + (jj & (hd - 1))) * 8;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {  // key groups h * 2 + lane / 32: registers 4h .. and 8 + 4h ..
+                    uint32_t w[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int r = (e >> 1) * 8 + h * 4 + (e & 1) * 2;
+                        w[e] = (uint32_t)f2bf(acc[i][j][r] + bias[j]) | ((uint32_t)f2bf(acc[i][j][r + 1] + bias[j]) << 16);
+                    }
+                    *reinterpret_cast<uint4*>(vb + (size_t)h * 2 * hd * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int jj = n0 + j * 32 + col - k_end;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int rl = b0 + (r >> 2) * 8 + rbase + (r & 3);
+                    if (rows.page[rl] < 0) continue;  // past M or unbacked
+                    bf16_t* vb = qa.pool + kv_block(g, qa.layer, rows.page[rl], jj >> lg_hd, 1);
+                    vb[v_index_bf16(g, rows.key[rl], jj & (hd - 1))] = f2bf(acc[i][j][r] + bias[j]);
+                }
+            }
+        }
+    }
+}
+
+template <int WGM, int WGN, int TM, int TN, int EPI>
+__global__ void __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(2)))
+gemm_wide_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __restrict__ C, int M, int N, int K,
+            int ldc, int m_tiles, int n_tiles, int nt0, int gm, int kps, size_t split_stride, QkvRopeArgs qa) {
+    constexpr int NW = WGM * WGN, BM = WGM * TM * 32, BN = WGN * TN * 32, WM = TM * 32, WN = TN * 32;
+    constexpr int AI = BM / 8 / NW, BI = BN / 8 / NW;  // 1 KB load instructions per wave per k-step
+    constexpr int NM = TM * TN, NR = TM + TN;          // MFMAs and fragment reads per cluster
+    static_assert(BM / 8 % NW == 0 && BN / 8 % NW == 0, "load split");
+    static_assert(EPI != EPI_SWIGLU || TN % 2 == 0, "SwiGLU pairs gate/up blocks inside a wave");
+    static_assert(EPI != EPI_QKV_ROPE || (TN == 4 && 64 * NW >= BM), "a wave's columns are whole heads");
+    __shared__ __attribute__((aligned(1024))) LdsStage<BM, BN> st0;
+    __shared__ __attribute__((aligned(1024))) LdsStage<BM, BN> st1;
+    const int w = xcd_remap(blockIdx.x, gridDim.x);
+    const int tiles = m_tiles * n_tiles, split = w / tiles;
+    int mt, nt;
+    wide_tile_of(w - split * tiles, m_tiles, n_tiles, gm, mt, nt);
+    nt += nt0;  // a launch may cover the column tiles from nt0 on
+    const int m0 = mt * BM;
+    const int k_begin = split * kps, k_end = min(K, k_begin + kps);
+    const int n_k = (k_end - k_begin) / kBK;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave / WGN, wc = wave % WGN;
+    const int a_bytes = (int)((size_t)M * K * 2), w_bytes = (int)((size_t)N * K * 2);
+
+    // lane l of load instruction j fills LDS chunk l % 8 of row l / 8 of its 8-row group
+    constexpr uint32_t kOut = 0x80000000u;
+    uint32_t a_off[AI], b_off[BI];
+#pragma unroll
+    for (int j = 0; j < AI; ++j) {
+        const int row = (wave * AI + j) * 8 + (lane >> 3), m = m0 + row;
+        a_off[j] = m < M ? (uint32_t)(((size_t)m * K + k_begin + lds_swizzle(row, lane & 7) * 8) * 2) : kOut;
+    }
+#pragma unroll
+    for (int j = 0; j < BI; ++j) {
+        const int row = (wave * BI + j) * 8 + (lane >> 3);
+        int n;
+        bool ok;
+        if (EPI == EPI_SWIGLU) {  // a wave's N range: WN/2 gate rows, then the up rows of the same columns
+            const int ff = N >> 1, rr = row % WN;
+            const int c = nt * (BN / 2) + row / WN * (WN / 2) + rr % (WN / 2);
+            ok = c < ff;
+            n = rr < WN / 2 ? c : ff + c;
+        } else {
+            n = nt * BN + row;
+            ok = n < N;
+        }
+        b_off[j] = ok ? (uint32_t)(((size_t)n * K + k_begin + lds_swizzle(row, lane & 7) * 8) * 2) : kOut;
+    }
+    auto load = [&](LdsStage<BM, BN>& sg, int k) {  // steps past the end read out of range: zeros
+        lds_dma_stage<AI, BI>(sg, A, a_bytes, W, w_bytes, a_off, b_off,
+                              k < n_k ? (uint32_t)k * kBK * 2 : 0x80000000u, wave, 0);
+    };
+    load(st0, 0);
+    load(st1, 1);
+
+    [[maybe_unused]] __shared__ WideQkvRows<EPI == EPI_QKV_ROPE ? BM : 32> qrows;
+    if constexpr (EPI == EPI_QKV_ROPE) wide_qkv_rows<BM>(qa, M, m0, tid, qrows);
+
+    f32x16_t acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    const int frow = lane & 31, fhalf = lane >> 5;
+    bf16x8_t af[2][TM], bfr[2][TN];
+    auto read = [&](bf16x8_t (&a)[TM], bf16x8_t (&b)[TN], const LdsStage<BM, BN>& sg, int ks) {
+        const int c = lds_swizzle(frow, ks * 2 + fhalf) << 3;  // the swizzle repeats every 16 rows
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+            a[i] = *reinterpret_cast<const bf16x8_t*>(&sg.a[(wr * WM + i * 32 + frow) * kBK + c]);
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+            b[j] = *reinterpret_cast<const bf16x8_t*>(&sg.b[(wc * WN + j * 32 + frow) * kBK + c]);
+    };
+    auto mma = [&](const bf16x8_t (&a)[TM], const bf16x8_t (&b)[TN]) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    };
+    wait_vmcnt_lds_reads<0>();  // (QKV: the row look-ups share the counter)
+    __builtin_amdgcn_s_barrier();
+    read(af[0], bfr[0], st0, 0);
+    // the schedule of a cluster: an MFMA, an LDS read, with LOADS a load, ...
+#define DASH_WIDE_SCHED(LOADS)                                                                    \
+    do {                                                                                          \
+        _Pragma("unroll") for (int q_ = 0; q_ < NM; ++q_) {                                       \
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                    \
+            __builtin_amdgcn_sched_group_barrier(0x100, (NR + NM - 1) / NM, 0);                   \
+            if (LOADS) __builtin_amdgcn_sched_group_barrier(0x020, (AI + BI + NM - 1) / NM, 0);   \
+        }                                                                                         \
+        __builtin_amdgcn_sched_barrier(0);                                                        \
+    } while (0)
+#define DASH_WIDE_STEP(CUR, NXT, KK)                                                              \
+    do {                                                                                          \
+        read(af[1], bfr[1], CUR, 1);                                                              \
+        mma(af[0], bfr[0]);                                                                       \
+        DASH_WIDE_SCHED(false);                                                                   \
+        read(af[0], bfr[0], CUR, 2);                                                              \
+        mma(af[1], bfr[1]);                                                                       \
+        DASH_WIDE_SCHED(false);                                                                   \
+        read(af[1], bfr[1], CUR, 3);                                                              \
+        mma(af[0], bfr[0]);                                                                       \
+        DASH_WIDE_SCHED(false);                                                                   \
+        wait_vmcnt_lds_reads<0>();                                                                \
+        __builtin_amdgcn_s_barrier();                                                             \
+        __builtin_amdgcn_sched_barrier(0);                                                        \
+        read(af[0], bfr[0], NXT, 0);                                                              \
+        load(CUR, (KK) + 2);                                                                      \
+        mma(af[1], bfr[1]);                                                                       \
+        DASH_WIDE_SCHED(true);                                                                    \
+    } while (0)
+    int k = 0;
+    for (; k + 2 <= n_k; k += 2) {
+        DASH_WIDE_STEP(st0, st1, k);
+        DASH_WIDE_STEP(st1, st0, k + 1);
+    }
+    if (k < n_k) DASH_WIDE_STEP(st0, st1, k);
+#undef DASH_WIDE_STEP
+#undef DASH_WIDE_SCHED
+    // the loads past the end still write their stages, and the last reads their registers
+    wait_vmcnt_lds_reads<0>();
+    __syncthreads();
+    if constexpr (EPI == EPI_QKV_ROPE) {
+        static_assert(NW / 2 * 32 * kQkvRow <= (BM + BN) * kBK, "staged rows fit the stages");
+        bf16_t* hs = (wave < NW / 2 ? st0.a : st1.a) + wave % (NW / 2) * (32 * kQkvRow);
+        wide_qkv_epilogue<BM, WM, TM>(acc, qa, M, N, m0, nt * BN + wc * WN, wr, lane, qrows, hs);
+    } else if constexpr (EPI == EPI_STORE_F32) {
+        store_f32_epilogue<BM, BN, WGM, WGN>(&acc[0][0], reinterpret_cast<float*>(C) + split * split_stride, M, N, ldc,
+                                             m0, nt, lane, wr, wc);
+    } else {
+        bf16_t* H = reinterpret_cast<bf16_t*>(C);
+        if (((ldc | (N >> 1)) & 7) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0) {
+            // each wave stages its own h tile in dead operand LDS (half the waves per stage), then
+            // stores 16-byte runs: no barrier between the waves
+            constexpr int OW = WN / 2, OS = OW + 8;
+            static_assert(NW / 2 * WM * OS <= (BM + BN) * kBK, "h tiles fit the stages");
+            static_assert(WM * OW / 8 % 64 == 0, "runs per lane");
+            bf16_t* Hs = (wave < NW / 2 ? st0.a : st1.a) + wave % (NW / 2) * (WM * OS);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN / 2; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        Hs[(i * 32 + (r >> 2) * 8 + fhalf * 4 + (r & 3)) * OS + j * 32 + frow] =
+                            f2bf(silu(acc[i][j][r]) * acc[i][j + TN / 2][r]);
+#pragma unroll
+            for (int u = 0; u < WM * OW / 8 / 64; ++u) {
+                const int run = lane + u * 64, rr = run / (OW / 8), c8 = run % (OW / 8) * 8;
+                const int m = m0 + wr * WM + rr, c = nt * (BN / 2) + wc * OW + c8;
+                if (m < M && c < (N >> 1))
+                    *reinterpret_cast<uint4*>(H + (size_t)m * ldc + c) = *reinterpret_cast<const uint4*>(Hs + rr * OS + c8);
+            }
+        } else {
+            swiglu_epilogue<BM, BN, WGM, WGN>(&acc[0][0], H, M, N, ldc, m0, nt, lane, wr, wc);
+        }
+    }
+}
+
+// Output columns [col0, col1) (SwiGLU: of h; col0 a multiple of the tile's output width).
+template <int WGM, int WGN, int TM, int TN, int EPI>
+hipError_t run_wide_cols(const void* A, const void* W, void* C, int M, int N, int K, int ldc, int nsplit,
+                         size_t split_stride, int col0, int col1, hipStream_t st,
+                         const QkvRopeArgs& qa = QkvRopeArgs{}) {
+    constexpr int BM = WGM * TM * 32, BN = WGN * TN * 32, tn = EPI == EPI_SWIGLU ? BN / 2 : BN;
+    const int m_tiles = (M + BM - 1) / BM, n_tiles = (col1 - col0 + tn - 1) / tn;
+    if (col0 < 0 || col0 % tn || col1 <= col0 || col1 > (EPI == EPI_SWIGLU ? N / 2 : N)) return hipErrorInvalidValue;
+    int kps = K;
+    if (nsplit > 1) kps = ((K + nsplit - 1) / nsplit + kBK - 1) / kBK * kBK;
+    if ((K + kps - 1) / kps != nsplit) return hipErrorInvalidValue;
+    if (K % kBK || (size_t)M * K * 2 >= (1u << 31) || (size_t)N * K * 2 >= (1u << 31)) return hipErrorInvalidValue;
+    // rows of tiles per block of the tile order: 6 x ~5 tiles at a time on an XCD where there
+    // are columns enough, 4 x 8 for the few column tiles of the projections back to d_model
+    // (measured 2-8 and 16: within 2% of the best of them on the prefill's shapes)
+    const int gm = n_tiles >= 16 ? 6 : 4;
+    gemm_wide_k<WGM, WGN, TM, TN, EPI><<<m_tiles * n_tiles * nsplit, 64 * WGM * WGN, 0, st>>>(
+        (const bf16_t*)A, (const bf16_t*)W, C, M, N, K, ldc, m_tiles, n_tiles, col0 / tn, gm, kps, split_stride, qa);
+    return hipGetLastError();
+}
+
+template <int WGM, int WGN, int TM, int TN, int EPI>
+hipError_t run_wide(const void* A, const void* W, void* C, int M, int N, int K, int ldc, int nsplit,
+                    size_t split_stride, hipStream_t st, const QkvRopeArgs& qa = QkvRopeArgs{}) {
+    return run_wide_cols<WGM, WGN, TM, TN, EPI>(A, W, C, M, N, K, ldc, nsplit, split_stride, 0,
+                                                EPI == EPI_SWIGLU ? N / 2 : N, st, qa);
+}
+
 template <int BM, int BN, int WGM, int WGN, int S, int EPI, int WPOL = 0>
 hipError_t run_lds(const void* A, const void* W, void* C, int M, int N, int K, int ldc, int nsplit,
                    size_t split_stride, hipStream_t st, const QkvRopeArgs& qa = QkvRopeArgs{}) {
@@ -742,6 +1090,19 @@ hipError_t launch_gemm_qkv_rope(const void* A, const void* W, int M, int N, int 
     if (!gemm_qkv_fusable(1, qa.n_heads, qa.g.n_kv, qa.g.head_dim) ||
         N != (qa.n_heads + 2 * qa.g.n_kv) * qa.g.head_dim)
         return hipErrorInvalidValue;
+    // Wide tiles where they fill the chip: 256x256 at one round (128-256 of them) or from one
+    // and a half on, else 128x128 (two per CU) from half a round on; below that 64x128, by
+    // direct-to-LDS loads while they fit one round (one per CU), else register-staged.  us
+    // at 1.5B / 3B (256x256, 128x128, 64x128 register-staged, weights cold): 2048 rows
+    // 44 25.5 27.4 / 52 34 45; 4206 rows 45 48 60 / 55 60 84; 10240 rows 77 72 124 / 102 119
+    // 185; 16384 rows 90 107 204 / 158 172 306.  64x128 direct-to-LDS at 419 rows: 10.1 vs
+    // 10.6 (0.5B), 13.1 vs 14.2, 15.5 vs 17.1; 3B at 1024 rows (320 tiles) 28.9 vs 26.0.
+    const long t256 = (long)((M + 255) / 256) * ((N + 255) / 256), t128 = (long)((M + 127) / 128) * (N / 128);
+    if ((t256 >= 128 && t256 <= 256) || t256 >= 384)
+        return run_wide<4, 2, 2, 4, EPI_QKV_ROPE>(A, W, nullptr, M, N, K, 0, 1, 0, st, qa);
+    if (t128 >= 256) return run_wide<4, 1, 1, 4, EPI_QKV_ROPE>(A, W, nullptr, M, N, K, 0, 1, 0, st, qa);
+    if ((long)((M + 63) / 64) * (N / 128) <= 256)
+        return run_lds<64, 128, 2, 4, 3, EPI_QKV_ROPE>(A, W, nullptr, M, N, K, 0, 1, 0, st, qa);
     return run_bf16<64, 128, 2, 4, 2, EPI_QKV_ROPE>(A, W, nullptr, M, N, K, 0, 1, 0, st, qa);
 }
 
@@ -775,7 +1136,7 @@ hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C
                     // 132.1 -> 114.5 us, 3B at 1024 rows 108.7 -> 96.9 us, 0.5B at 2048 rows
                     // 44.9 -> 43.0 us (a last round at least half full runs whole, as below).
                     const int c_split = (int)split_tiles * 128;
-                    hipError_t e = run_bf16_swiglu_cols<256, 256, 4, 4, 2>(A, W, C, M, N, K, ldc, 0, c_split, st);
+                    hipError_t e = run_wide_cols<2, 4, 4, 2, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, 0, c_split, st);
                     if (e != hipSuccess) return e;
                     const long rc = ff - c_split, m128 = (M + 127) / 128;
                     if (m128 * ((rc + 127) / 128) >= 128)
@@ -785,21 +1146,16 @@ hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C
                     return run_bf16_swiglu_cols<64, 128, 2, 2, 2>(A, W, C, M, N, K, ldc, c_split, ff, st);
                 }
                 // Past 384 rows the tile is chosen by how its work-groups fill the 256 CUs
-                // (one 256x256 or 128x256 work-group per CU, two 128x128 ones): 256x256 where
-                // they fill one round (128-256 tiles), or leave a last round at least half
-                // full, or run four rounds or more; else 128x256 under the same test; else
-                // 128x128.  Measured with dash_gemm_bench on the 0.5B, 1.5B and 3B shapes at
-                // 512-2048 rows (weights cold, interleaved rounds): each choice the fastest
-                // tiling or within 2% of it (256x256: 1.5B 7% / 19% faster than 128x128 at
-                // 512 / 768 rows, 3B 13% at 2048; 128x128: 0.5B 20% faster than 256x256 at
-                // 2048 rows); 256x256 also measured 15-19% faster at 4096-16384 rows.
-                const long cols = (N / 2 + 127) / 128;
-                const long t256 = (M + 255) / 256 * cols, t128 = (M + 127) / 128 * cols;
+                // (one 256x256 work-group per CU, two 128x128 ones): 256x256 where they fill
+                // one round (128-256 tiles), or leave a last round at least half full, or run
+                // four rounds or more; else 128x128.  us, 256x256 / 128x128 (0.5B, the width
+                // that has few tiles): 419 rows 19.8 / 13.6, 768 rows 20.4 / 16.5, 1024 rows
+                // 21.3 / 25.2, 2048 rows 44.9 / 40.7; 1.5B at 512 rows 41.5 / 53.4, 3B at 2048
+                // rows 160 / 197.
+                const long t256 = mb * ((N / 2 + 127) / 128);
                 if ((t256 >= 128 && t256 <= 256) || t256 % 256 >= 128 || t256 >= 4 * 256)
-                    return run_bf16<256, 256, 4, 4, 2, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
-                if (t128 <= 256 || t128 % 256 >= 128)
-                    return run_bf16<128, 256, 4, 4, 2, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
-                return run_bf16<128, 128, 4, 2, 2, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
+                    return run_wide<2, 4, 4, 2, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
+                return run_wide<2, 2, 2, 2, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
             }
             if (M > 256) return run_bf16<128, 128, 4, 2, 2, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
             // Small batches: 64 column pairs per tile read the batch rows half as often as
@@ -820,6 +1176,11 @@ hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C
                                                                                split_stride, st);
             if (M <= 128)  // measured 10-18% faster than 256x256 at 96-128 rows
                 return run_bf16<128, 256, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
+            // wide tiles where a tile's chain is long enough to pay for their start-up: 1.5B 2%
+            // faster at 1024 rows, 9% at 8192; K = 896 up to 1024 rows, and one 256-row block
+            // at K = 2048, 1-2% slower
+            if (M > 256 && (K >= 1024 || M > 1024))
+                return run_wide<2, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             return run_bf16<256, 256, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
         }
         if (K < 4096 && M >= 256 && M <= 4096) {
@@ -862,7 +1223,7 @@ hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C
                 return run_lds<128, 128, 2, 2, 4, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             if (M <= 1024)
                 return run_bf16<128, 256, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
-            return run_bf16<256, 256, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
+            return run_wide<2, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
         }
         if (M <= 512)
             return run_bf16<64, 64, 2, 2, 3, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
@@ -870,7 +1231,7 @@ hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C
             return run_bf16<64, 64, 2, 2, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
         if (M <= 4096)
             return run_bf16<128, 128, 4, 2, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
-        return run_bf16<256, 256, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
+        return run_wide<2, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
     }
     if (nsplit != 1) return hipErrorInvalidValue;
     if (epi == EPI_SWIGLU) {

@@ -101,3 +101,29 @@ def test_pg_loss_edge_cases():
     assert abs(float(loss.item()) - 1.0 / 3.0) < 1e-15
     loss, _ = engine.pg_loss(lp, adv, dev_i32([]))  # nothing kept
     assert float(loss.item()) == 0.0
+
+
+# name, layers, d_model, heads, kv heads, head dim, d_ff, vocab: d_model of one, five and three 64-deep k-steps,
+# vocabularies past the LM head's tile width
+WIDE_A = synth.Shape("wide-hd64", 2, 320, 8, 2, 64, 448, 8200, 1e6, synth.DT_BF16)
+WIDE_B = synth.Shape("wide-hd128", 1, 192, 6, 2, 128, 576, 8193, 1e6, synth.DT_BF16)
+WIDE_C = synth.Shape("wide-k64", 1, 64, 6, 1, 64, 64, 300, 1e6, synth.DT_BF16)
+
+
+@pytest.mark.parametrize("shape,n,P,L_", [(WIDE_A, 8, 600, 701),    # 128x128 QKV tiles, rows off the pages
+                                          (WIDE_A, 16, 650, 704),   # 256x256 QKV tiles, whole pages of keys
+                                          (WIDE_B, 5, 640, 701), (WIDE_B, 10, 660, 701),
+                                          (WIDE_C, 65, 500, 512)])
+def test_wide_tiles_bit_identical_to_small_batches(shape, n, P, L_):
+    """Many sequences in one forward pass (the wide GEMM tiles, their last row and column tiles
+    partly empty, the QKV projection's RoPE and KV append from the accumulators) give the bits of
+    one sequence at a time on the small tiles."""
+    w = synth.make_weights(shape, 21)
+    _, _, seqs = _seqs(shape, n, P, L_ - P, 21)
+    model = engine.Model(shape, w)
+    kv = make_kv(model, 32, n, L_)
+    a = engine.teacher_forced_logprobs(model, kv, dev_i32(seqs), P, seqs_per_chunk=n).cpu().numpy()
+    kv.pool.zero_()
+    b = engine.teacher_forced_logprobs(model, kv, dev_i32(seqs), P, seqs_per_chunk=1).cpu().numpy()
+    assert np.isfinite(a).all()
+    np.testing.assert_array_equal(a.view(np.uint32), b.view(np.uint32))
