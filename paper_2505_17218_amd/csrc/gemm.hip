@@ -943,6 +943,223 @@ hipError_t run_wide(const void* A, const void* W, void* C, int M, int N, int K, 
                                                 EPI == EPI_SWIGLU ? N / 2 : N, st, qa);
 }
 
+// ---- small batches ---------------------------------------------------------------
+// Up to a few row blocks the projections are chains of dependent k-steps in few work-groups:
+// what a step costs is latency.  (Register-staged tiles four steps ahead took ~0.2 us per
+// 64-deep step on every shape and batch up to 64 rows, cold or cached, where the four MFMAs
+// of a step take 0.053.)  So the tiles are narrow, one 32 x 32 block (or U of its columns) or
+// two per wave, and up to S = 8 steps of both operands are on their way into LDS at once; a
+// step's fragments are read while the step before is multiplied, so a step is a wait for
+// the oldest load, a barrier and four MFMAs.  U < 32 leaves a block's other columns unused
+// (the fragments repeat): more work-groups over the same weights.
+//
+// Column blocks: TN consecutive ones (fp32 store), or gate columns then the up columns of the
+// same h columns (SwiGLU).  (With the QKV projection's RoPE and KV append in the epilogue the
+// one launch took 7.7-12 us at 16-64 rows against 7.6-10.4 for this kernel and the append
+// kernel: few waves chase the page look-ups and scattered stores; not kept.)  Measured (weights cold, against the register-staged 64 x 32 .. 64 x 256 tiles it replaced):
+// QKV / O at 16 rows 0.5B 5.8 -> 4.4 us, 1.5B 7.7 -> 5.5, 3B 9.3 -> 6.6; down 5.4 -> 4.6,
+// 8.9 -> 7.1, 12.5 -> 10.5; gate/up 9.0 -> 6.7, 14.3 -> 12.5, 21.7 -> 20.6; LM head (weights
+// at 5.9 TB/s) 59 -> 47, 93 -> 78, 132 -> 106.  Same fragments and MFMA order: same bits.
+template <int WM_, int WN_, int TN, int U, int S, int EPI, int WPOL>
+__global__ void __launch_bounds__(64 * WM_ * WN_)
+gemm_stream_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __restrict__ C, int M, int N, int K,
+              int ldc, int m_tiles, int n_tiles, int kps, size_t split_stride) {
+    constexpr int NW = WM_ * WN_, BM = 32 * WM_, WN = U * TN, BN = WN * WN_;
+    constexpr int AI = BM / 8 / NW, BI = BN / 8 / NW, DPS = AI + BI;  // 1 KB loads per wave per k-step
+    static_assert(BM / 8 % NW == 0 && BN / 8 % NW == 0 && BI >= 1, "load split");
+    static_assert((S - 1) * DPS < 64, "loads in flight fit the counter");
+    static_assert(S == 3 || S == 4 || S == 8, "stages");
+    static_assert(U == 8 || U == 16 || U == 32, "columns per block");
+    static_assert(EPI == EPI_STORE_F32 || (EPI == EPI_SWIGLU && TN == 2), "SwiGLU holds a gate / up pair in a lane");
+    using Stage = LdsStage<BM, BN>;
+#define DASH_STAGE(i)                                                                                            \
+    __shared__ __attribute__((aligned(1024))) LdsStage<(S > i ? BM : 8), (S > i ? BN : 8)> st##i##_;             \
+    Stage& st##i = *reinterpret_cast<Stage*>(&st##i##_);
+    DASH_STAGE(0) DASH_STAGE(1) DASH_STAGE(2) DASH_STAGE(3)
+    DASH_STAGE(4) DASH_STAGE(5) DASH_STAGE(6) DASH_STAGE(7)
+#undef DASH_STAGE
+    const int w = xcd_remap(blockIdx.x, gridDim.x);
+    const int mt = w % m_tiles, rest = w / m_tiles, nt = rest % n_tiles, split = rest / n_tiles;
+    const int m0 = mt * BM;
+    const int k_begin = split * kps, k_end = min(K, k_begin + kps);
+    const int n_k = (k_end - k_begin) / kBK;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave / WN_, wc = wave % WN_;
+    const int frow = lane & 31, fhalf = lane >> 5;
+    const int a_bytes = (int)((size_t)M * K * 2), w_bytes = (int)((size_t)N * K * 2);
+    constexpr uint32_t kOut = 0x80000000u;
+    uint32_t a_off[AI], b_off[BI];
+#pragma unroll
+    for (int j = 0; j < AI; ++j) {
+        const int row = (wave * AI + j) * 8 + (lane >> 3), m = m0 + row;
+        a_off[j] = m < M ? (uint32_t)(((size_t)m * K + k_begin + lds_swizzle(row, lane & 7) * 8) * 2) : kOut;
+    }
+#pragma unroll
+    for (int j = 0; j < BI; ++j) {
+        const int row = (wave * BI + j) * 8 + (lane >> 3);
+        int n;
+        bool ok;
+        if (EPI == EPI_SWIGLU) {  // U gate rows, then the up rows of the same columns
+            const int c = (nt * WN_ + row / WN) * U + row % U;
+            ok = c < (N >> 1);
+            n = row % WN < U ? c : (N >> 1) + c;
+        } else {
+            n = nt * BN + row;
+            ok = n < N;
+        }
+        b_off[j] = ok ? (uint32_t)(((size_t)n * K + k_begin + lds_swizzle(row, lane & 7) * 8) * 2) : kOut;
+    }
+    auto load = [&](Stage& sg, int k) {  // steps past the end read out of range: zeros
+        lds_dma_stage<AI, BI>(sg, A, a_bytes, W, w_bytes, a_off, b_off,
+                              k < n_k ? (uint32_t)k * kBK * 2 : 0x80000000u, wave, WPOL);
+    };
+    load(st0, 0);
+    load(st1, 1);
+    load(st2, 2);
+    if constexpr (S > 3) load(st3, 3);
+    if constexpr (S > 4) {
+        load(st4, 4);
+        load(st5, 5);
+        load(st6, 6);
+        load(st7, 7);
+    }
+    f32x16_t acc[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+    bf16x8_t af[2][4], bfr[2][4][TN];
+    auto read = [&](bf16x8_t (&a)[4], bf16x8_t (&b)[4][TN], const Stage& sg) {
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const int c = ks * 2 + fhalf, ar = wr * 32 + frow;
+            a[ks] = *reinterpret_cast<const bf16x8_t*>(&sg.a[ar * kBK + (lds_swizzle(ar, c) << 3)]);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int br = wc * WN + j * U + frow % U;
+                b[ks][j] = *reinterpret_cast<const bf16x8_t*>(&sg.b[br * kBK + (lds_swizzle(br, c) << 3)]);
+            }
+        }
+    };
+    auto mma = [&](const bf16x8_t (&a)[4], const bf16x8_t (&b)[4][TN]) {
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks], b[ks][j], acc[j], 0, 0, 0);
+    };
+    wait_vmcnt_lds_reads<(S - 1) * DPS>();
+    __builtin_amdgcn_s_barrier();
+    read(af[0], bfr[0], st0);
+    // Step KK from fragment set P (its stage CUR is all in registers of every wave once past
+    // the barrier, so CUR is refilled) while NXT's fragments are read into the other set.
+#define DASH_STREAM_STEP(P, CUR, NXT, KK)          \
+    do {                                           \
+        wait_vmcnt_lds_reads<(S - 2) * DPS>();     \
+        __builtin_amdgcn_s_barrier();              \
+        __builtin_amdgcn_sched_barrier(0);         \
+        read(af[1 - (P)], bfr[1 - (P)], NXT);      \
+        load(CUR, (KK) + S);                       \
+        mma(af[P], bfr[P]);                        \
+        __builtin_amdgcn_sched_barrier(0);         \
+    } while (0)
+#define DASH_STREAM_TAIL(P, CUR, NXT)              \
+    if (k < n_k) {                                 \
+        DASH_STREAM_STEP(P, CUR, NXT, k);          \
+        ++k;                                       \
+    }
+    int k = 0;
+    if constexpr (S == 3) {
+        for (; k + 6 <= n_k; k += 6) {
+            DASH_STREAM_STEP(0, st0, st1, k);
+            DASH_STREAM_STEP(1, st1, st2, k + 1);
+            DASH_STREAM_STEP(0, st2, st0, k + 2);
+            DASH_STREAM_STEP(1, st0, st1, k + 3);
+            DASH_STREAM_STEP(0, st1, st2, k + 4);
+            DASH_STREAM_STEP(1, st2, st0, k + 5);
+        }
+        DASH_STREAM_TAIL(0, st0, st1)
+        DASH_STREAM_TAIL(1, st1, st2)
+        DASH_STREAM_TAIL(0, st2, st0)
+        DASH_STREAM_TAIL(1, st0, st1)
+        DASH_STREAM_TAIL(0, st1, st2)
+    } else if constexpr (S == 4) {
+        for (; k + 4 <= n_k; k += 4) {
+            DASH_STREAM_STEP(0, st0, st1, k);
+            DASH_STREAM_STEP(1, st1, st2, k + 1);
+            DASH_STREAM_STEP(0, st2, st3, k + 2);
+            DASH_STREAM_STEP(1, st3, st0, k + 3);
+        }
+        DASH_STREAM_TAIL(0, st0, st1)
+        DASH_STREAM_TAIL(1, st1, st2)
+        DASH_STREAM_TAIL(0, st2, st3)
+    } else {
+        for (; k + 8 <= n_k; k += 8) {
+            DASH_STREAM_STEP(0, st0, st1, k);
+            DASH_STREAM_STEP(1, st1, st2, k + 1);
+            DASH_STREAM_STEP(0, st2, st3, k + 2);
+            DASH_STREAM_STEP(1, st3, st4, k + 3);
+            DASH_STREAM_STEP(0, st4, st5, k + 4);
+            DASH_STREAM_STEP(1, st5, st6, k + 5);
+            DASH_STREAM_STEP(0, st6, st7, k + 6);
+            DASH_STREAM_STEP(1, st7, st0, k + 7);
+        }
+        DASH_STREAM_TAIL(0, st0, st1)
+        DASH_STREAM_TAIL(1, st1, st2)
+        DASH_STREAM_TAIL(0, st2, st3)
+        DASH_STREAM_TAIL(1, st3, st4)
+        DASH_STREAM_TAIL(0, st4, st5)
+        DASH_STREAM_TAIL(1, st5, st6)
+        DASH_STREAM_TAIL(0, st6, st7)
+    }
+#undef DASH_STREAM_TAIL
+#undef DASH_STREAM_STEP
+    if constexpr (EPI == EPI_STORE_F32) {
+        float* Cp = reinterpret_cast<float*>(C) + split * split_stride;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int n = nt * BN + wc * WN + j * U + frow;
+            if (n < N && frow < U)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int m = m0 + wr * 32 + (r >> 2) * 8 + fhalf * 4 + (r & 3);
+                    if (m < M) Cp[(size_t)m * ldc + n] = acc[j][r];
+                }
+        }
+    } else {
+        bf16_t* H = reinterpret_cast<bf16_t*>(C);
+        const int c = (nt * WN_ + wc) * U + frow;
+        if (c < (N >> 1) && frow < U)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int m = m0 + wr * 32 + (r >> 2) * 8 + fhalf * 4 + (r & 3);
+                if (m < M) H[(size_t)m * ldc + c] = f2bf(silu(acc[0][r]) * acc[1][r]);
+            }
+    }
+    wait_vmcnt<0>();  // the out-of-range loads of the steps past the end still write their stages
+}
+
+template <int WM_, int WN_, int TN, int U, int S, int EPI>
+hipError_t run_stream(const void* A, const void* W, void* C, int M, int N, int K, int ldc, int nsplit,
+                      size_t split_stride, hipStream_t st) {
+    constexpr int BM = 32 * WM_, BN = U * TN * WN_;
+    const int m_tiles = (M + BM - 1) / BM, n_tiles = (N + BN - 1) / BN;
+    int kps = K;
+    if (nsplit > 1) kps = ((K + nsplit - 1) / nsplit + kBK - 1) / kBK * kBK;
+    if ((K + kps - 1) / kps != nsplit) return hipErrorInvalidValue;
+    if (K % kBK || (size_t)M * K * 2 >= (1u << 31) || (size_t)N * K * 2 >= (1u << 31)) return hipErrorInvalidValue;
+    const int blocks = m_tiles * n_tiles * nsplit;
+    // a weight byte that one work-group alone reads streams past the caches
+    if (m_tiles == 1)
+        gemm_stream_k<WM_, WN_, TN, U, S, EPI, 2><<<blocks, 64 * WM_ * WN_, 0, st>>>(
+            (const bf16_t*)A, (const bf16_t*)W, C, M, N, K, ldc, m_tiles, n_tiles, kps, split_stride);
+    else
+        gemm_stream_k<WM_, WN_, TN, U, S, EPI, 0><<<blocks, 64 * WM_ * WN_, 0, st>>>(
+            (const bf16_t*)A, (const bf16_t*)W, C, M, N, K, ldc, m_tiles, n_tiles, kps, split_stride);
+    return hipGetLastError();
+}
+
 template <int BM, int BN, int WGM, int WGN, int S, int EPI, int WPOL = 0>
 hipError_t run_lds(const void* A, const void* W, void* C, int M, int N, int K, int ldc, int nsplit,
                    size_t split_stride, hipStream_t st, const QkvRopeArgs& qa = QkvRopeArgs{}) {
@@ -1106,11 +1323,6 @@ hipError_t launch_gemm_qkv_rope(const void* A, const void* W, int M, int N, int 
     return run_bf16<64, 128, 2, 4, 2, EPI_QKV_ROPE>(A, W, nullptr, M, N, K, 0, 1, 0, st, qa);
 }
 
-// Cache policy of the weight loads where the batch fits one 64-row block: every
-// weight byte is then read by exactly one work-group, so the loads stream past the
-// caches (the same non-temporal policy as the decode attention's private K/V loads).
-constexpr int kWeightStream = 2;
-
 hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C, int M, int N, int K, int ldc,
                        int nsplit, size_t split_stride, hipStream_t st) {
     if (M <= 0 || N <= 0) return hipSuccess;
@@ -1158,22 +1370,23 @@ hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C
                 return run_wide<2, 2, 2, 2, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
             }
             if (M > 256) return run_bf16<128, 128, 4, 2, 2, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
-            // Small batches: 64 column pairs per tile read the batch rows half as often as
-            // 32; worth it where that still leaves >= 128 work-groups per 64-row block
-            // (d_ff >= 8192).  Measured on the 1.5B and 3B shapes: 9-11% faster up to 64
-            // rows (three k-steps in flight), 5-16% at 129-256 rows, 3-5% slower at 65-128.
-            if ((N / 2 + 63) / 64 >= 128) {
-                if (M <= 64)
-                    return run_bf16<64, 128, 2, 2, 3, EPI_SWIGLU, kWeightStream>(A, W, C, M, N, K, ldc, 1, 0, st);
-                if (M > 128) return run_bf16<64, 128, 2, 2, 2, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
-            }
-            if (M <= 64) return run_bf16<64, 64, 2, 1, 2, EPI_SWIGLU, kWeightStream>(A, W, C, M, N, K, ldc, 1, 0, st);
-            return run_bf16<64, 64, 2, 1, 2, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
+            // Small batches: the streaming kernel, on the narrowest tile (h columns) of those
+            // below that reads the batch rows no more often than it pays.  us at 48-64 rows,
+            // 32 / 64 columns: 0.5B 7.8 / 9.5, 3B 25.3 / 22.0; 128 rows, 64 x 64 / 128 x 64:
+            // 0.5B 9.9 / 12.3, 1.5B 27.7 / 20.3, 3B 35.1 / 26.4 (register-staged before: 11.4,
+            // 24.7, 32.5).  129-256 rows with more tiles than CUs stay register-staged (1.5B
+            // 25.4 against 27-35 us at 192 rows).
+            const long t64 = (N / 2 + 63) / 64;
+            if (M <= 32) return run_stream<1, 1, 2, 16, 4, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
+            if (M <= 64 && t64 < 128) return run_stream<2, 1, 2, 32, 4, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
+            if ((M + 63) / 64 * t64 <= 256) return run_stream<2, 2, 2, 32, 4, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
+            if ((M + 127) / 128 * t64 <= 256) return run_stream<4, 2, 2, 32, 4, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
+            return run_bf16<64, 128, 2, 2, 2, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
         }
         if (N >= 8192) {  // LM head: many tiles, the largest tile that the batch fills wins
-            if (M <= 64)
-                return run_bf16<64, 256, 1, 4, 2, EPI_STORE_F32, kWeightStream>(A, W, C, M, N, K, ldc, nsplit,
-                                                                               split_stride, st);
+            // one row block: two work-groups of four 32 x 32 (eight) blocks a CU
+            if (M <= 32) return run_stream<1, 4, 1, 32, 4, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
+            if (M <= 64) return run_stream<2, 4, 1, 32, 3, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             if (M <= 128)  // measured 10-18% faster than 256x256 at 96-128 rows
                 return run_bf16<128, 256, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             // wide tiles where a tile's chain is long enough to pay for their start-up: 1.5B 2%
@@ -1182,6 +1395,31 @@ hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C
             if (M > 256 && (K >= 1024 || M > 1024))
                 return run_wide<2, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             return run_bf16<256, 256, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
+        }
+        // Small launches of the other projections: the streaming kernel, on the smallest tile
+        // that gives no more work-groups than CUs (short reductions: 32 rows x 16 columns,
+        // 32 x 32, 64 x 32; the split down projection, whose rows are fewer but longer, up
+        // to 128 x 64).  us against the register-staged tiles at 128 / 256 rows: QKV 0.5B 5.0
+        // / 6.1 (6.0 / 6.7), 1.5B 6.3 / 8.1 (8.0 / 9.5); down 0.5B 6.3 / 8.1 (6.7 / 9.3), 1.5B
+        // 11.6 / 15.6 (12.3 / 19.0), 3B 16.5 / 22.2 (17.7 / 27.9).  A tile past one round loses
+        // (3B QKV at 192 rows on 480 32 x 32 tiles 10.8, on 240 64 x 32 tiles 9.9).
+        const auto tiles = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * nsplit; };
+        if (K < 4096) {
+            if (tiles(32, 16) <= 256)
+                return run_stream<1, 1, 1, 16, 8, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
+            if (tiles(32, 32) <= 256)
+                return run_stream<1, 1, 1, 32, 8, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
+            if (tiles(64, 32) <= 256)
+                return run_stream<2, 1, 1, 32, 8, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
+        } else {  // split counts give up to 288 tiles per row block
+            if (tiles(32, 32) <= 288)
+                return run_stream<1, 1, 1, 32, 8, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
+            if (tiles(64, 32) <= 288)
+                return run_stream<2, 1, 1, 32, 8, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
+            if (tiles(64, 64) <= 288)
+                return run_stream<2, 2, 1, 32, 4, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
+            if (tiles(128, 64) <= 288)
+                return run_stream<4, 2, 1, 32, 4, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
         }
         if (K < 4096 && M >= 256 && M <= 4096) {
             // Unsplit short reductions (the output projection; QKV where it is not fused):
@@ -1197,26 +1435,16 @@ hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C
                 return run_lds<128, 64, 2, 2, 4, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             return run_lds<128, 128, 2, 2, 4, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
         }
-        if (M <= 256 && (K < 4096 || M <= 64)) {
-            // Few work-groups stream the weights here; four k-steps in flight per thread
-            // instead of two pull them faster while the launch is small (unsplit K, or one
-            // 64-row block): measured 22-28% faster on the 1.5B and 3B QKV / O shapes up to
-            // 256 rows and on the split down projection up to 64 rows.
-            if (M <= 64)
-                return run_bf16<64, 32, 2, 1, 4, EPI_STORE_F32, kWeightStream>(A, W, C, M, N, K, ldc, nsplit,
-                                                                              split_stride, st);
+        // wide projections at up to 256 rows: narrow tiles, four k-steps in flight per thread
+        if (M <= 256 && K < 4096)
             return run_bf16<64, 32, 2, 1, 4, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
-        }
         // Larger batches: the largest tile that still gives the launch enough work-groups.
         // Measured crossovers on the 0.5B, 1.5B and 3B shapes: the split down projection
-        // 64x64 three k-steps ahead up to 128 rows and two up to 384 (12-19% faster than
-        // 64x32 there), the direct-to-LDS 128x128 tiles up to 640, 128x256 up to 1024,
+        // 64x64 up to 384 rows (12-19% faster than 64x32 there), the direct-to-LDS 128x128 tiles up to 640, 128x256 up to 1024,
         // 256x256 past that (12-18% faster from 1536 rows); QKV / O 64x64 three k-steps ahead up to 512 rows (10-15% faster than two),
         // 64x64 up to 1024, 128x128 up to 4096 (4-30% faster from 1536), 256x256 past that
         // (15-26% faster at 8192-16384).
         if (K >= 4096) {
-            if (M <= 128)
-                return run_bf16<64, 64, 2, 2, 3, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             if (M <= 384)
                 return run_bf16<64, 64, 2, 2, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             if (M <= 640)  // direct-to-LDS 128x128: 23-35% faster at 512 rows on all three shapes

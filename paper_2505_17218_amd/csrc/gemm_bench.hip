@@ -207,7 +207,7 @@ struct QkvCase {
 // read by one work-group) and each work-group's k-loop is a chain of dependent loads,
 // so the variants differ in how many k-steps each thread keeps in flight.
 void bench_small(const ModelShape* shapes, int n_shapes, int reps, hipStream_t st, std::mt19937& rng) {
-    constexpr int W = kWeightStream;
+    constexpr int W = 2;  // non-temporal weight loads
     char label[128];
     for (int si = 0; si < n_shapes; ++si) {
         const ModelShape& sh = shapes[si];
