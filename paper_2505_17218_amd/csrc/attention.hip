@@ -17,7 +17,8 @@
 // workgroups and merged by a second kernel in a fixed order (deterministic).
 //
 // Prefill (bf16): the same MFMA block step with the 16 columns being 16
-// consecutive query positions of one head, masked causally per column.
+// consecutive query positions of one head, masked causally per column; the heads
+// of a kv head share its key blocks through LDS.
 //
 // Generic (fp32 caches): one wave per (row, query head), scores with lanes over
 // keys and the value sum with lanes over dims.
@@ -37,7 +38,8 @@ constexpr float kLog2e = 1.4426950408889634f;
 // Blocks below KVGeom::shared_keys (a prompt group's shared pages, read by all the
 // group's rows at about the same time) keep the default policy.
 // Prefill keeps the default: each key block is read again by every 16-query column
-// block of its sequence and should stay cached (streaming it measured 1.75x slower).
+// block of its sequence and should stay cached (streaming it measured 1.75x slower with
+// a wave per head).
 constexpr int kKvStream = 2, kKvReuse = 0;
 
 // s_waitcnt vmcnt(n), the other counters left alone (gfx9 encoding, n < 64)
@@ -162,9 +164,8 @@ DASH_DEV void attn_block(AttnState<HD>& st, KVRegs<HD>& r, const bf16x8_t (&qf)[
     for (int i = 0; i < 4; ++i) {
         const float p0 = __builtin_amdgcn_exp2f(t[2 * i] - ref), p1 = __builtin_amdgcn_exp2f(t[2 * i + 1] - ref);
         psum += p0 + p1;
-        const bf16_t h0 = f2bf(p0), h1 = f2bf(p1);
-        pk[i] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-        pl[i] = (uint32_t)f2bf(p0 - bf2f(h0)) | ((uint32_t)f2bf(p1 - bf2f(h1)) << 16);
+        pk[i] = f2bf2(p0, p1);
+        pl[i] = f2bf2(p0 - __uint_as_float(pk[i] << 16), p1 - __uint_as_float(pk[i] & 0xFFFF0000u));
     }
     st.l = st.l * alpha + psum;
     const bf16x8_t pf = __builtin_bit_cast(bf16x8_t, make_uint4(pk[0], pk[1], pk[2], pk[3]));
@@ -204,9 +205,8 @@ DASH_DEV void attn_store(const AttnState<HD>& st, float l, bf16_t* orow, int grp
     const float inv = l > 0.f ? 1.0f / l : 0.f;
 #pragma unroll
     for (int d = 0; d < HD / 16; ++d) {
-        const uint32_t lo = (uint32_t)f2bf(st.acc[d][0] * inv) | ((uint32_t)f2bf(st.acc[d][1] * inv) << 16);
-        const uint32_t hi = (uint32_t)f2bf(st.acc[d][2] * inv) | ((uint32_t)f2bf(st.acc[d][3] * inv) << 16);
-        *reinterpret_cast<uint2*>(orow + d * 16 + grp * 4) = make_uint2(lo, hi);
+        *reinterpret_cast<uint2*>(orow + d * 16 + grp * 4) =
+            make_uint2(f2bf2(st.acc[d][0] * inv, st.acc[d][1] * inv), f2bf2(st.acc[d][2] * inv, st.acc[d][3] * inv));
     }
 }
 
@@ -433,53 +433,133 @@ __global__ void __launch_bounds__(512) decode_attn_prefix_k(const bf16_t* __rest
 }
 
 // ---- prefill ---------------------------------------------------------------
-// One wave per (prompt, query head, 16 consecutive query positions), causal.
-// Rows of a prompt are contiguous: row = prompt * P + position.
-
+// Causal attention of whole prompts (rows of a prompt are contiguous: row = prompt * P +
+// position).  A work-group serves the query heads of one kv head (or half of them) and nq
+// blocks of 16 consecutive positions: one wave per (head, block).  All its waves attend the
+// same keys, so the 32-key blocks go through a ring of three LDS slots, copied verbatim from
+// the cache pages by direct-to-LDS loads two blocks ahead: each block is fetched once per
+// work-group and not once per wave.  Column by column the arithmetic is attn_block's, so the
+// bits are those of the decode chain.
+//
+// What bounds it: each block's chain of MFMAs and softmax arithmetic in a wave (24 MFMAs of
+// 16x16x32 at head dim 128, about 780 cycles, and as many of vector arithmetic), at three
+// waves per SIMD.  With a wave per (head, 16 positions) reading K/V into registers it was
+// bound by load latency and L2 traffic.  Per layer, before / after: 64 prompts of 256 tokens
+// at 12 heads of 128 131 / 87 us, 8 sequences of 1280 192 / 162, 6 of 701 at 14 heads of 64
+// 41 / 39 (few work-groups: the longest chain of blocks sets the time).
 template <int HD>
-__global__ void __launch_bounds__(64) prefill_attn_bf16_k(const bf16_t* __restrict__ q, const int32_t* __restrict__ slot,
-                                                          const int32_t* __restrict__ page_table,
-                                                          const bf16_t* __restrict__ pool, KVGeom g, int layer,
-                                                          int n_heads, int P, bf16_t* __restrict__ o, float scale_log2) {
-    constexpr int NC = HD / 32;
-    const int lane = threadIdx.x, col = lane & 15, grp = lane >> 4;
-    const int qblocks = (P + 15) >> 4;
-    const int prompt = blockIdx.x / qblocks, q0 = (blockIdx.x % qblocks) * 16;
-    const int h = blockIdx.y, kvh = h / (n_heads / g.n_kv);
+struct KVSlot {
+    bf16_t k[32 * HD];  // [HD / 32][32 keys][32 dims]
+    bf16_t v[32 * HD];  // [4 key groups][HD][8 keys]
+};
+
+// Copy one 32-key block into a slot: HD / 8 units of 1 KB, U per wave (units past the block go
+// to sink).  An unbacked page, or a block past the end, reads as zeros.
+template <int HD, int U>
+DASH_DEV void kv_slot_load(KVSlot<HD>& sl, uint32_t* sink, const bf16_t* pool, const KVGeom& g, int layer, int kvh,
+                           int page, int kin, int wave, int nw, int lane) {
+    constexpr int KU = HD / 16;  // units of K (and of V)
+    const int blk_bytes = g.page_size * HD * 2;
+    const bool ok = page >= 0;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t*>(pool + kv_block(g, layer, ok ? page : 0, kvh, 0)), 0, ok ? 2 * blk_bytes : 0, kBufferDword3);
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+        const int u = wave + i * nw;  // wave-uniform
+        const bool in = u < 2 * KU, is_v = u >= KU;
+        const int off = is_v ? blk_bytes + (kin >> 5) * (HD * 64) + (u - KU) * 1024
+                             : ((u >> 1) * g.page_size + kin) * 64 + (u & 1) * 1024;
+        char* dst = in ? reinterpret_cast<char*>(&sl) + u * 1024 : reinterpret_cast<char*>(sink);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)dst, 16,
+                                                 in ? off + lane * 16 : 0x80000000u, 0, 0, kKvReuse);
+    }
+}
+
+template <int HD, int U>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3)))
+prefill_attn_bf16_k(const bf16_t* __restrict__ q, const int32_t* __restrict__ slot,
+                    const int32_t* __restrict__ page_table, const bf16_t* __restrict__ pool, KVGeom g, int layer,
+                    int n_heads, int P, bf16_t* __restrict__ o, float scale_log2, int wg_heads, int nq) {
+    constexpr int NC = HD / 32, ND = HD / 16;
+    __shared__ __attribute__((aligned(1024))) KVSlot<HD> s0;
+    __shared__ __attribute__((aligned(1024))) KVSlot<HD> s1;
+    __shared__ __attribute__((aligned(1024))) KVSlot<HD> s2;
+    __shared__ __attribute__((aligned(1024))) uint32_t sink[256];
+    const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = wg_heads * nq;
+    const int rep = n_heads / g.n_kv, chunks = (rep + wg_heads - 1) / wg_heads;
+    const int kvh = blockIdx.y / chunks, hl = (blockIdx.y % chunks) * wg_heads + wave / nq;
+    const int qtiles = (P + 16 * nq - 1) / (16 * nq);
+    const int prompt = blockIdx.x / qtiles, qt = qtiles - 1 - blockIdx.x % qtiles;  // longest first
+    const int q0 = (qt * nq + wave % nq) * 16;
+    const int h = kvh * rep + hl;
+    const bool busy = hl < rep && q0 < P;    // the wave has a head and a query
     const int qp = q0 + col;                 // this column's query position
-    const bool valid = qp < P;
-    const int row = prompt * P + (valid ? qp : q0);
+    const bool valid = busy && qp < P;
+    const size_t row = (size_t)prompt * P + (valid ? qp : min(q0, P - 1));
     const int sl = slot[(size_t)prompt * P];
     const int last = min(P, q0 + 16);        // keys < last are written
+    const int my_blk = busy ? (last + 31) >> 5 : 0;
+    const int nblk = (min(P, (qt + 1) * nq * 16) + 31) >> 5;
+    // The next block to copy: its number, key within the page, page-table column and entry.  The
+    // entry is read a step ahead and checked when it is used, so that the read's latency is
+    // not waited for.
+    const bool slot_ok = sl >= 0 && sl < g.max_seqs;
+    const int32_t* trow = page_table + (size_t)(slot_ok ? sl : 0) * g.max_pages;
+    int nb = 0, kin = 0, pi = 0, entry = trow[0];
+    auto load = [&](KVSlot<HD>& dst) {
+        const bool ok = slot_ok && nb < nblk && pi < g.max_pages && entry >= 0 && entry < g.n_pages;
+        kv_slot_load<HD, U>(dst, sink, pool, g, layer, kvh, ok ? entry : -1, kin, wave, nw, lane);
+        ++nb;
+        kin += 32;
+        if (kin == g.page_size) {
+            kin = 0;
+            ++pi;
+        }
+        entry = trow[min(pi, g.max_pages - 1)];
+    };
+    load(s0);
+    load(s1);
     bf16x8_t qf[NC];
     {
-        const bf16_t* qrow = q + ((size_t)row * n_heads + h) * HD;
+        const bf16_t* qrow = q + (row * n_heads + (hl < rep ? h : 0)) * HD;
 #pragma unroll
         for (int c = 0; c < NC; ++c) qf[c] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(qrow + c * 32 + grp * 8));
     }
     AttnState<HD> st;
     attn_init(st);
     const int lim = valid ? qp + 1 : 1;
-    const int nblk = (last + 31) >> 5;
-    KVRegs<HD> r[2];
-    auto fetch = [&](KVRegs<HD>& dst, int b) {
-        const int key0 = b << 5;
-        int page = kv_page_of(g, page_table, sl, key0);
-        const bool ok = page >= 0;
-        page = ok ? page : 0;
-        load_kv<HD, kKvReuse>(dst, pool + kv_block(g, layer, page, kvh, 0), pool + kv_block(g, layer, page, kvh, 1),
-                              g.page_size, key0 % g.page_size, ok, col, grp);
+    // Block b: its own copies have landed (those of b + 1 may be in flight) and, past the
+    // barrier, every wave's; every wave has also read the slot of block b - 1, which block
+    // b + 2 refills.
+    auto step = [&](const KVSlot<HD>& cur, KVSlot<HD>& fill, int b) {
+        __builtin_amdgcn_s_waitcnt(0x0070 | (U & 15) | ((U >> 4) << 14));  // vmcnt(U) lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        load(fill);
+        if (b < my_blk) {
+            KVRegs<HD> r;
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+                    r.k[hh][c] = *reinterpret_cast<const uint4*>(&cur.k[(c * 32 + hh * 16 + col) * 32 + grp * 8]);
+#pragma unroll
+            for (int d = 0; d < ND; ++d)
+                r.v[d] = *reinterpret_cast<const uint4*>(&cur.v[(grp * HD + d * 16 + col) * 8]);
+            attn_block<HD>(st, r, qf, b << 5, lim, last, scale_log2, grp);
+        }
     };
-    fetch(r[0], 0);
-    for (int b = 0; b < nblk; b += 2) {
-        fetch(r[1], min(b + 1, nblk - 1));
-        attn_block<HD>(st, r[0], qf, b << 5, lim, last, scale_log2, grp);
-        if (b + 1 >= nblk) break;
-        fetch(r[0], min(b + 2, nblk - 1));
-        attn_block<HD>(st, r[1], qf, (b + 1) << 5, lim, last, scale_log2, grp);
+    int b = 0;
+    for (; b + 3 <= nblk; b += 3) {
+        step(s0, s2, b);
+        step(s1, s0, b + 1);
+        step(s2, s1, b + 2);
     }
+    if (b < nblk) step(s0, s2, b++);
+    if (b < nblk) step(s1, s0, b++);
+    vm_wait<0>();  // the copies past the end still write their slots
     const float l = attn_denominator(st);
-    if (valid) attn_store<HD>(st, l, o + ((size_t)row * n_heads + h) * HD, grp);
+    if (valid) attn_store<HD>(st, l, o + (row * n_heads + h) * HD, grp);
 }
 
 // Merge the context splits of rows that have more than one, in split order:
@@ -725,16 +805,30 @@ hipError_t launch_prefill_attention(int dtype, const void* q, const int32_t* pos
     if (rows <= 0) return hipSuccess;
     const float scale = 1.0f / sqrtf((float)g.head_dim);
     if (dtype == 1 && prompt_len > 0 && rows % prompt_len == 0) {
-        dim3 grid((rows / prompt_len) * ((prompt_len + 15) / 16), n_heads);
+        // 4 to 8 waves per work-group: up to 8 of the kv head's query heads (more in two halves),
+        // and 2 or 4 blocks of 16 positions where the heads are few
+        const int rep = n_heads / g.n_kv;
+        const int wg_heads = rep <= 8 ? rep : (rep + 1) / 2, chunks = (rep + wg_heads - 1) / wg_heads;
+        const int nq = wg_heads == 1 ? 4 : wg_heads <= 3 ? 2 : 1, nw = wg_heads * nq;
+        const int prompts = rows / prompt_len, qtiles = (prompt_len + 16 * nq - 1) / (16 * nq);
+        dim3 grid(prompts * qtiles, g.n_kv * chunks);
         const float sl2 = scale * kLog2e;
-        if (g.head_dim == 128)
-            prefill_attn_bf16_k<128><<<grid, 64, 0, st>>>((const bf16_t*)q, slot, page_table, (const bf16_t*)pool, g,
-                                                           layer, n_heads, prompt_len, (bf16_t*)o, sl2);
+#define DASH_PREFILL(HD, U)                                                                                     \
+    prefill_attn_bf16_k<HD, U><<<grid, 64 * nw, 0, st>>>((const bf16_t*)q, slot, page_table, (const bf16_t*)pool, \
+                                                         g, layer, n_heads, prompt_len, (bf16_t*)o, sl2, wg_heads, nq)
+        if (g.head_dim == 128 && nw == 8)
+            DASH_PREFILL(128, 2);
+        else if (g.head_dim == 128 && nw >= 6)
+            DASH_PREFILL(128, 3);
+        else if (g.head_dim == 128)
+            DASH_PREFILL(128, 4);
+        else if (g.head_dim == 64 && nw == 8)
+            DASH_PREFILL(64, 1);
         else if (g.head_dim == 64)
-            prefill_attn_bf16_k<64><<<grid, 64, 0, st>>>((const bf16_t*)q, slot, page_table, (const bf16_t*)pool, g,
-                                                          layer, n_heads, prompt_len, (bf16_t*)o, sl2);
+            DASH_PREFILL(64, 2);
         else
             return hipErrorInvalidValue;
+#undef DASH_PREFILL
         return hipGetLastError();
     }
     dim3 grid(rows, n_heads);

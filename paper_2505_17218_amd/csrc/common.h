@@ -26,6 +26,13 @@ DASH_DEV float bf2f(bf16_t u) { return __uint_as_float(static_cast<uint32_t>(u) 
 // 2^32 inputs, NaNs included; dash_bf16_round_check verifies that on the device in use.
 DASH_DEV bf16_t f2bf(float f) { return __builtin_bit_cast(bf16_t, static_cast<__bf16>(f)); }
 
+// Two values at once, a in the low half: one conversion instruction, the bits of f2bf.
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+DASH_DEV uint32_t f2bf2(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
+}
+
 // The same rounding on the integer bit pattern: add 0x7FFF plus the lowest kept bit and
 // truncate; a NaN keeps its top half with the quiet bit set.
 DASH_DEV bf16_t bf16_rne_bits(float f) {

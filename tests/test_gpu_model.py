@@ -653,3 +653,22 @@ def test_stale_nonfinite_pool_bytes_do_not_change_results(shape, P, T):
     for x, y in zip(outs[False], outs[True]):
         assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
     np.testing.assert_array_equal(outs[True][0], runs[True, False].tokens)
+
+
+@pytest.mark.parametrize("hd,n_heads,n_kv", [(64, 2, 2), (64, 4, 2), (64, 6, 2), (64, 7, 1), (64, 9, 1), (64, 16, 1),
+                                             (128, 1, 1), (128, 2, 1), (128, 3, 1), (128, 5, 1), (128, 8, 1), (128, 11, 1)])
+def test_prefill_attention_head_groups(hd, n_heads, n_kv):
+    """Prefill attention over every size of head group (waves per work-group, heads in two
+    halves, several position blocks per work-group), at lengths around the 16-position and
+    32-key blocks and past three blocks, against the oracle."""
+    shape = synth.Shape("heads", 1, 128, n_heads, n_kv, hd, 128, 300, 1e6, synth.DT_BF16)
+    w = synth.make_weights(shape, 31)
+    model = engine.Model(shape, w)
+    for P in (1, 16, 17, 33, 64, 131):
+        wl = synth.Workload("t", shape, 2, 1, P, 1)
+        prompts = synth.make_prompts(wl, P)
+        kv = engine.KVCache(model, 64 if P > 64 else 32, 2, P + 1, 2 * (P // 32 + 2))
+        got = engine.prefill(model, kv, dev_i32(prompts), 1, [0, 1]).cpu().numpy()
+        for n in range(2):
+            want = om.rollout_logits(shape_dict(shape), w, prompts[n], np.zeros(1, np.int32))[0]
+            assert np.abs(got[n] - want).max() <= 3e-2, (P, n)
