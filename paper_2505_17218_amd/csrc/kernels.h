@@ -146,9 +146,11 @@ hipError_t launch_sample(const float* logits, int64_t ld, int rows, int vocab, c
 hipError_t launch_logprob_gather(const float* logits, int64_t ld, int rows, int vocab, const int32_t* tokens, int per,
                                  int stride, int off, float* lp_out, hipStream_t st);
 // Per row pair: D_KL(softmax(base) || softmax(theta)) into kl and the reverse
-// direction into kl_rev (may be null); -inf logits have probability zero.
+// direction into kl_rev (may be null); -inf logits have probability zero.  lp_out (may be
+// null): launch_logprob_gather's log-probs of `tokens` under theta too, the same bits.
 hipError_t launch_logits_kl(const float* theta, const float* base, int64_t ld, int rows, int vocab, float* kl,
-                            float* kl_rev, hipStream_t st);
+                            float* kl_rev, hipStream_t st, const int32_t* tokens = nullptr, int per = 1,
+                            int stride = 0, int off = 0, float* lp_out = nullptr);
 // *loss = -(1/n_total) sum over kept samples n of A[n] * sum_{t < len[n]} lp[n][t] (float64);
 // seq_lp[n] (nullable) receives each kept sample's sequence log-prob.
 hipError_t launch_pg_loss(const float* lp, int64_t ld, int T, const int32_t* len, const float* adv,

@@ -1239,11 +1239,9 @@ int dash_teacher_forced_kl(dash_model* m, dash_model* base, dash_kv* kv, const i
         // the base model first: its cache entries are then overwritten by the policy's
         if ((rc = tf_forward(base, kv, w, tok, rows, rows_lm, L, t.logits_base, st))) return rc;
         if ((rc = tf_forward(m, kv, w, tok, rows, rows_lm, L, t.logits, st))) return rc;
-        if (d_lp)
-            DASH_HIP(launch_logprob_gather(t.logits, d.vocab, rows_lm, d.vocab, tok, Tg, L, P, d_lp + (size_t)s0 * Tg,
-                                           st));
         DASH_HIP(launch_logits_kl(t.logits, t.logits_base, d.vocab, rows_lm, d.vocab, d_kl + (size_t)s0 * Tg,
-                                  d_kl_rev ? d_kl_rev + (size_t)s0 * Tg : nullptr, st));
+                                  d_kl_rev ? d_kl_rev + (size_t)s0 * Tg : nullptr, st, tok, Tg, L, P,
+                                  d_lp ? d_lp + (size_t)s0 * Tg : nullptr));
         guard.armed = false;
         if ((rc = dash_kv_release(kv, slots.data(), nc))) return rc;
     }
