@@ -91,7 +91,8 @@ DASH_DEV void wait_vmcnt_lds_reads() {
 // acc[i * TN + j][r] of a wave holds row (r / 4) * 8 + (lane / 32) * 4 + r % 4 and column
 // lane % 32 of its 32 x 32 block (i, j).
 
-template <int BM, int BN, int WGM, int WGN>
+// NT: streaming stores, for an output larger than the last-level cache
+template <int BM, int BN, int WGM, int WGN, bool NT = false>
 DASH_DEV void store_f32_epilogue(const f32x16_t* acc, float* Cp, int M, int N, int ldc, int m0, int nt, int lane,
                                  int wr, int wc) {
     constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
@@ -105,7 +106,9 @@ DASH_DEV void store_f32_epilogue(const f32x16_t* acc, float* Cp, int M, int N, i
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int m = m0 + wr * WM + i * 32 + (r >> 2) * 8 + rbase + (r & 3);
-                if (m < M) Cp[(size_t)m * ldc + n] = acc[i * TN + j][r];
+                if (m >= M) continue;
+                if constexpr (NT) __builtin_nontemporal_store(acc[i * TN + j][r], &Cp[(size_t)m * ldc + n]);
+                else Cp[(size_t)m * ldc + n] = acc[i * TN + j][r];
             }
         }
 }
@@ -617,6 +620,8 @@ gemm_lds_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __r
 // half lines (four or five of them in flight) were 5-10% slower, and touching the lines of
 // later steps (one dword per 64 bytes) 6-12%: the vector memory path, 64 bytes a cycle
 // and CU, is half busy already, so requests cost more than the latency they would hide.
+// Where a launch has at most one tile per CU nothing hides a late load, and half-size tiles with
+// three stages in flight win (256 x 128; the weights come from HBM there).
 // Same fragments and MFMA order as the other kernels: identical bits.
 
 // Tile order: blocks of gm tile rows, column by column inside a block, so that the ~32
@@ -750,7 +755,7 @@ DASH_DEV void wide_qkv_epilogue(const f32x16_t (&acc)[TM][4], const QkvRopeArgs&
     }
 }
 
-template <int WGM, int WGN, int TM, int TN, int EPI>
+template <int WGM, int WGN, int TM, int TN, int EPI, int S, bool NT>
 __global__ void __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(2)))
 gemm_wide_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __restrict__ C, int M, int N, int K,
             int ldc, int m_tiles, int n_tiles, int nt0, int gm, int kps, size_t split_stride, QkvRopeArgs qa) {
@@ -758,10 +763,15 @@ gemm_wide_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __
     constexpr int AI = BM / 8 / NW, BI = BN / 8 / NW;  // 1 KB load instructions per wave per k-step
     constexpr int NM = TM * TN, NR = TM + TN;          // MFMAs and fragment reads per cluster
     static_assert(BM / 8 % NW == 0 && BN / 8 % NW == 0, "load split");
+    static_assert(S >= 2 && S <= 4 && (S - 1) * (AI + BI) < 64, "stages");
     static_assert(EPI != EPI_SWIGLU || TN % 2 == 0, "SwiGLU pairs gate/up blocks inside a wave");
     static_assert(EPI != EPI_QKV_ROPE || (TN == 4 && 64 * NW >= BM), "a wave's columns are whole heads");
     __shared__ __attribute__((aligned(1024))) LdsStage<BM, BN> st0;
     __shared__ __attribute__((aligned(1024))) LdsStage<BM, BN> st1;
+    __shared__ __attribute__((aligned(1024))) LdsStage<(S > 2 ? BM : 8), (S > 2 ? BN : 8)> st2_;
+    __shared__ __attribute__((aligned(1024))) LdsStage<(S > 3 ? BM : 8), (S > 3 ? BN : 8)> st3_;
+    [[maybe_unused]] LdsStage<BM, BN>& st2 = *reinterpret_cast<LdsStage<BM, BN>*>(&st2_);
+    [[maybe_unused]] LdsStage<BM, BN>& st3 = *reinterpret_cast<LdsStage<BM, BN>*>(&st3_);
     const int w = xcd_remap(blockIdx.x, gridDim.x);
     const int tiles = m_tiles * n_tiles, split = w / tiles;
     int mt, nt;
@@ -805,6 +815,8 @@ gemm_wide_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __
     };
     load(st0, 0);
     load(st1, 1);
+    if constexpr (S > 2) load(st2, 2);
+    if constexpr (S > 3) load(st3, 3);
 
     [[maybe_unused]] __shared__ WideQkvRows<EPI == EPI_QKV_ROPE ? BM : 32> qrows;
     if constexpr (EPI == EPI_QKV_ROPE) wide_qkv_rows<BM>(qa, M, m0, tid, qrows);
@@ -835,7 +847,7 @@ gemm_wide_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __
             for (int j = 0; j < TN; ++j)
                 acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
     };
-    wait_vmcnt_lds_reads<0>();  // (QKV: the row look-ups share the counter)
+    wait_vmcnt_lds_reads<EPI == EPI_QKV_ROPE ? 0 : (S - 1) * (AI + BI)>();  // (QKV: the row look-ups count too)
     __builtin_amdgcn_s_barrier();
     read(af[0], bfr[0], st0, 0);
     // the schedule of a cluster: an MFMA, an LDS read, with LOADS a load, ...
@@ -859,20 +871,40 @@ gemm_wide_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __
         read(af[1], bfr[1], CUR, 3);                                                              \
         mma(af[0], bfr[0]);                                                                       \
         DASH_WIDE_SCHED(false);                                                                   \
-        wait_vmcnt_lds_reads<0>();                                                                \
+        wait_vmcnt_lds_reads<(S - 2) * (AI + BI)>();                                              \
         __builtin_amdgcn_s_barrier();                                                             \
         __builtin_amdgcn_sched_barrier(0);                                                        \
         read(af[0], bfr[0], NXT, 0);                                                              \
-        load(CUR, (KK) + 2);                                                                      \
+        load(CUR, (KK) + S);                                                                      \
         mma(af[1], bfr[1]);                                                                       \
         DASH_WIDE_SCHED(true);                                                                    \
     } while (0)
     int k = 0;
-    for (; k + 2 <= n_k; k += 2) {
-        DASH_WIDE_STEP(st0, st1, k);
-        DASH_WIDE_STEP(st1, st0, k + 1);
+    if constexpr (S == 2) {
+        for (; k + 2 <= n_k; k += 2) {
+            DASH_WIDE_STEP(st0, st1, k);
+            DASH_WIDE_STEP(st1, st0, k + 1);
+        }
+        if (k < n_k) DASH_WIDE_STEP(st0, st1, k);
+    } else if constexpr (S == 3) {
+        for (; k + 3 <= n_k; k += 3) {
+            DASH_WIDE_STEP(st0, st1, k);
+            DASH_WIDE_STEP(st1, st2, k + 1);
+            DASH_WIDE_STEP(st2, st0, k + 2);
+        }
+        if (k < n_k) DASH_WIDE_STEP(st0, st1, k);
+        if (k + 1 < n_k) DASH_WIDE_STEP(st1, st2, k + 1);
+    } else {
+        for (; k + 4 <= n_k; k += 4) {
+            DASH_WIDE_STEP(st0, st1, k);
+            DASH_WIDE_STEP(st1, st2, k + 1);
+            DASH_WIDE_STEP(st2, st3, k + 2);
+            DASH_WIDE_STEP(st3, st0, k + 3);
+        }
+        if (k < n_k) DASH_WIDE_STEP(st0, st1, k);
+        if (k + 1 < n_k) DASH_WIDE_STEP(st1, st2, k + 1);
+        if (k + 2 < n_k) DASH_WIDE_STEP(st2, st3, k + 2);
     }
-    if (k < n_k) DASH_WIDE_STEP(st0, st1, k);
 #undef DASH_WIDE_STEP
 #undef DASH_WIDE_SCHED
     // the loads past the end still write their stages, and the last reads their registers
@@ -883,8 +915,8 @@ gemm_wide_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __
         bf16_t* hs = (wave < NW / 2 ? st0.a : st1.a) + wave % (NW / 2) * (32 * kQkvRow);
         wide_qkv_epilogue<BM, WM, TM>(acc, qa, M, N, m0, nt * BN + wc * WN, wr, lane, qrows, hs);
     } else if constexpr (EPI == EPI_STORE_F32) {
-        store_f32_epilogue<BM, BN, WGM, WGN>(&acc[0][0], reinterpret_cast<float*>(C) + split * split_stride, M, N, ldc,
-                                             m0, nt, lane, wr, wc);
+        store_f32_epilogue<BM, BN, WGM, WGN, NT>(&acc[0][0], reinterpret_cast<float*>(C) + split * split_stride, M, N,
+                                                 ldc, m0, nt, lane, wr, wc);
     } else {
         bf16_t* H = reinterpret_cast<bf16_t*>(C);
         if (((ldc | (N >> 1)) & 7) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0) {
@@ -916,7 +948,7 @@ gemm_wide_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __
 }
 
 // Output columns [col0, col1) (SwiGLU: of h; col0 a multiple of the tile's output width).
-template <int WGM, int WGN, int TM, int TN, int EPI>
+template <int WGM, int WGN, int TM, int TN, int EPI, int S = 2>
 hipError_t run_wide_cols(const void* A, const void* W, void* C, int M, int N, int K, int ldc, int nsplit,
                          size_t split_stride, int col0, int col1, hipStream_t st,
                          const QkvRopeArgs& qa = QkvRopeArgs{}) {
@@ -930,17 +962,28 @@ hipError_t run_wide_cols(const void* A, const void* W, void* C, int M, int N, in
     // rows of tiles per block of the tile order: 6 x ~5 tiles at a time on an XCD where there
     // are columns enough, 4 x 8 for the few column tiles of the projections back to d_model
     // (measured 2-8 and 16: within 2% of the best of them on the prefill's shapes)
-    const int gm = n_tiles >= 16 ? 6 : 4;
-    gemm_wide_k<WGM, WGN, TM, TN, EPI><<<m_tiles * n_tiles * nsplit, 64 * WGM * WGN, 0, st>>>(
+    const int gm = n_tiles >= 16 ? 6 : 4, blocks = m_tiles * n_tiles * nsplit;
+    // An fp32 output past the 256 MB last-level cache leaves by streaming stores, which keep
+    // the operands in L2 (its reader misses either way): LM head 1.5B 3896 -> 3775 us at 8192
+    // rows, 512 -> 505 at 1024; the five partials of the down projection at 16,384 rows 439
+    // -> 426.  Smaller outputs are read from that cache next.
+    constexpr size_t kCache = (size_t)256 << 20;
+    if constexpr (EPI == EPI_STORE_F32)
+        if ((size_t)M * (col1 - col0) * nsplit * 4 > kCache) {
+            gemm_wide_k<WGM, WGN, TM, TN, EPI, S, true><<<blocks, 64 * WGM * WGN, 0, st>>>(
+                (const bf16_t*)A, (const bf16_t*)W, C, M, N, K, ldc, m_tiles, n_tiles, col0 / tn, gm, kps, split_stride, qa);
+            return hipGetLastError();
+        }
+    gemm_wide_k<WGM, WGN, TM, TN, EPI, S, false><<<blocks, 64 * WGM * WGN, 0, st>>>(
         (const bf16_t*)A, (const bf16_t*)W, C, M, N, K, ldc, m_tiles, n_tiles, col0 / tn, gm, kps, split_stride, qa);
     return hipGetLastError();
 }
 
-template <int WGM, int WGN, int TM, int TN, int EPI>
+template <int WGM, int WGN, int TM, int TN, int EPI, int S = 2>
 hipError_t run_wide(const void* A, const void* W, void* C, int M, int N, int K, int ldc, int nsplit,
                     size_t split_stride, hipStream_t st, const QkvRopeArgs& qa = QkvRopeArgs{}) {
-    return run_wide_cols<WGM, WGN, TM, TN, EPI>(A, W, C, M, N, K, ldc, nsplit, split_stride, 0,
-                                                EPI == EPI_SWIGLU ? N / 2 : N, st, qa);
+    return run_wide_cols<WGM, WGN, TM, TN, EPI, S>(A, W, C, M, N, K, ldc, nsplit, split_stride, 0,
+                                                   EPI == EPI_SWIGLU ? N / 2 : N, st, qa);
 }
 
 // ---- small batches ---------------------------------------------------------------
@@ -1367,6 +1410,10 @@ hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C
                 const long t256 = mb * ((N / 2 + 127) / 128);
                 if ((t256 >= 128 && t256 <= 256) || t256 % 256 >= 128 || t256 >= 4 * 256)
                     return run_wide<2, 4, 4, 2, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
+                // one round of 256x128 with three stages: 0.5B at 419 rows 14.9 -> 13.5 us, at 768
+                // rows 17.5 -> 16.7
+                if (mb * ((ff + 63) / 64) <= 256)
+                    return run_wide<4, 2, 2, 2, EPI_SWIGLU, 3>(A, W, C, M, N, K, ldc, 1, 0, st);
                 return run_wide<2, 2, 2, 2, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
             }
             if (M > 256) return run_bf16<128, 128, 4, 2, 2, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
@@ -1389,10 +1436,9 @@ hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C
             if (M <= 64) return run_stream<2, 4, 1, 32, 3, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             if (M <= 128)  // measured 10-18% faster than 256x256 at 96-128 rows
                 return run_bf16<128, 256, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
-            // wide tiles where a tile's chain is long enough to pay for their start-up: 1.5B 2%
-            // faster at 1024 rows, 9% at 8192; K = 896 up to 1024 rows, and one 256-row block
-            // at K = 2048, 1-2% slower
-            if (M > 256 && (K >= 1024 || M > 1024))
+            // wide tiles past one 256-row block (there 2% slower at K = 2048): 0.5B at 419 rows 169
+            // -> 163 us, 1.5B at 1024 rows 516 -> 505, at 8192 rows 9%
+            if (M > 256)
                 return run_wide<2, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             return run_bf16<256, 256, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
         }
@@ -1431,6 +1477,10 @@ hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C
             // 128x64 for the 0.5B shape at 768-1024 rows
             if ((long)((M + 63) / 64) * ((N + 63) / 64) <= 256)
                 return run_lds<64, 64, 2, 2, 4, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
+            // 128x128 with eight waves and four stages where they fit one round and 128x64 tiles
+            // would start a second: 1.5B at 1665 rows 21.6 -> 14.2 us
+            if (tiles(128, 64) > 256 && tiles(128, 128) <= 192)
+                return run_wide<4, 2, 1, 2, EPI_STORE_F32, 4>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             if (M <= 1024 || (long)(M / 128) * ((N + 127) / 128) < 160)
                 return run_lds<128, 64, 2, 2, 4, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             return run_lds<128, 128, 2, 2, 4, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
@@ -1449,6 +1499,11 @@ hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C
                 return run_bf16<64, 64, 2, 2, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             if (M <= 640)  // direct-to-LDS 128x128: 23-35% faster at 512 rows on all three shapes
                 return run_lds<128, 128, 2, 2, 4, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
+            // 256x128 with three stages while one round holds them and a split's chain is long:
+            // 1.5B / 3B at 768 rows 32.1 -> 28.4 us / 49.8 -> 43.0, at 1024 rows 34.8 -> 31.2 /
+            // 53.6 -> 47.2; 0.5B (ten k-steps a split) 16.9 -> 18.1, not used
+            if (tiles(256, 128) <= 256 && K / nsplit >= 1024)
+                return run_wide<4, 2, 2, 2, EPI_STORE_F32, 3>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             if (M <= 1024)
                 return run_bf16<128, 256, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             return run_wide<2, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
