@@ -22,6 +22,7 @@
 #include "kernels.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace dash {
 
@@ -947,6 +948,245 @@ gemm_wide_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __
     }
 }
 
+// ---- wide tiles, persistent ---------------------------------------------------------
+// gemm_wide_k's 256 x 256 tile (eight waves of 128 x 64, two stages) in work-groups that stay:
+// one per CU, each walking its share of its XCD's run of tiles.  The last two k-steps of a
+// tile already load the next tile's first two, and the output leaves by 16-byte stores that
+// drain under the next tile's first step, so a tile costs its k-steps and a short epilogue
+// and not also a load latency and the draining of its output.  (In gemm_wide_k the stores of
+// the 1.5B LM head at 8192 rows cost 600 of 3740 us and the rest per tile 6 of 42 us.)
+//
+// The output tile passes through LDS of the wave's own (kOutLds bytes a wave beside the two
+// stages): 16 rows of fp32 or 32 rows of h at a time.  Every store instruction is issued
+// whatever its lanes' bounds (rows and columns outside the output get an offset past the
+// buffer's extent and are dropped), so the number of stores between two loads is known: the
+// first step of a tile waits for all but them (loads and stores of a wave complete in order).
+// An odd step count is padded with a step of zeros, which changes no bit (an accumulator is
+// never -0).
+constexpr int kOutLds = 4096;
+
+struct WideTile {
+    int m0, n0, split;  // n0: first output column (SwiGLU: of h)
+};
+
+template <int EPI, bool NT>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+gemm_wide_persist_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __restrict__ C, int M, int N, int K,
+                    int ldc, int m_tiles, int n_tiles, int nt0, int gm, int kps, size_t split_stride, int tiles) {
+    constexpr int WGN = 4, TM = 4, TN = 2, BM = 256, BN = 256, WM = 128, WN = 64, AI = 4, BI = 4;
+    constexpr int NM = TM * TN, NR = TM + TN;
+    constexpr int kStores = EPI == EPI_STORE_F32 ? 32 : 8;  // store instructions per wave and tile
+    __shared__ __attribute__((aligned(1024))) LdsStage<BM, BN> st0;
+    __shared__ __attribute__((aligned(1024))) LdsStage<BM, BN> st1;
+    __shared__ __attribute__((aligned(1024))) char out_lds[8 * kOutLds];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave / WGN, wc = wave % WGN;
+    const int frow = lane & 31, fhalf = lane >> 5;
+    // this work-group's tiles: t, t + step, ... below t_end
+    const int x = blockIdx.x % kXcds, q = tiles / kXcds, rem = tiles % kXcds;
+    const int t_end = x * q + min(x, rem) + q + (x < rem);
+    const int t_step = gridDim.x / kXcds;
+    int t = x * q + min(x, rem) + blockIdx.x / kXcds;
+    if (t >= t_end) return;  // the grid is a multiple of the XCD count: a short run leaves blocks idle
+
+    constexpr uint32_t kOut = 0x80000000u;
+    auto tile_at = [&](int w) {
+        const int split = w / (m_tiles * n_tiles);
+        int mt, nt;
+        wide_tile_of(w - split * m_tiles * n_tiles, m_tiles, n_tiles, gm, mt, nt);
+        return WideTile{mt * BM, (nt + nt0) * (EPI == EPI_SWIGLU ? BN / 2 : BN), split};
+    };
+    auto steps_of = [&](const WideTile& tl) { return (min(K, tl.split * kps + kps) - tl.split * kps) / kBK; };
+    // The wave's operand rows of a tile: 32 rows of A and 32 weight rows (SwiGLU: even waves the
+    // gate rows of their pair's 32 columns, odd waves the up rows), consecutive in memory, so
+    // a base, the bytes from it to the operand's end (rows past it read as zeros; gate rows
+    // past the last column read up rows, whose outputs are dropped) and two lane offsets
+    // (the swizzle alternates between 8-row groups) address them all.
+    struct Rows {
+        const bf16_t *a, *w;
+        int a_left, w_left;
+    };
+    auto rows_of = [&](const WideTile& tl) {
+        const int k_begin = tl.split * kps, m = tl.m0 + wave * 32;
+        const int n = EPI == EPI_SWIGLU ? tl.n0 + (wave >> 1) * 32 + (wave & 1) * (N >> 1) : tl.n0 + wave * 32;
+        return Rows{A + (size_t)m * K + k_begin, W + (size_t)n * K + k_begin,
+                    m < M ? (int)(((size_t)(M - m) * K - k_begin) * 2) : 0,
+                    n < N ? (int)(((size_t)(N - n) * K - k_begin) * 2) : 0};
+    };
+    const uint32_t l_off[2] = {(uint32_t)((lane >> 3) * K * 2 + ((lane & 7) ^ (lane >> 4)) * 16),
+                               (uint32_t)((lane >> 3) * K * 2 + ((lane & 7) ^ (4 + (lane >> 4))) * 16)};
+    auto load = [&](LdsStage<BM, BN>& sg, const Rows& rw, int k, int n_k) {  // a step past the end reads zeros
+        const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(rw.a), 0, k < n_k ? rw.a_left : 0, kBufferDword3);
+        const __amdgpu_buffer_rsrc_t rsW = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(rw.w), 0, k < n_k ? rw.w_left : 0, kBufferDword3);
+#pragma unroll
+        for (int j = 0; j < AI; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lds_void*)&sg.a[(wave * AI + j) * 8 * kBK], 16,
+                                                     l_off[j & 1] + (uint32_t)(j * 16 * K + k * kBK * 2), 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < BI; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsW, (lds_void*)&sg.b[(wave * BI + j) * 8 * kBK], 16,
+                                                     l_off[j & 1] + (uint32_t)(j * 16 * K + k * kBK * 2), 0, 0, 0);
+    };
+
+    WideTile tile = tile_at(t);
+    int n_k = steps_of(tile);
+    Rows rows = rows_of(tile);
+    load(st0, rows, 0, n_k);
+    load(st1, rows, 1, n_k);
+
+    f32x16_t acc[TM][TN];
+    bf16x8_t af[2][TM], bfr[2][TN];
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    };
+    auto read = [&](bf16x8_t (&a)[TM], bf16x8_t (&b)[TN], const LdsStage<BM, BN>& sg, int ks) {
+        const int c = lds_swizzle(frow, ks * 2 + fhalf) << 3;  // the swizzle repeats every 16 rows
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+            a[i] = *reinterpret_cast<const bf16x8_t*>(&sg.a[(wr * WM + i * 32 + frow) * kBK + c]);
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+            b[j] = *reinterpret_cast<const bf16x8_t*>(&sg.b[(wc * WN + j * 32 + frow) * kBK + c]);
+    };
+    auto mma = [&](const bf16x8_t (&a)[TM], const bf16x8_t (&b)[TN]) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    };
+    // The output tile of the finished accumulators.  The lane index is made opaque, so that the
+    // dozens of addresses built from it are formed here and not kept in registers through the
+    // k-loop (which then spilled).
+    auto store = [&](const WideTile& tl) {
+        typedef unsigned u32x4_t __attribute__((__vector_size__(4 * sizeof(unsigned)), __may_alias__));
+        typedef float f32_lds_t __attribute__((__may_alias__));
+        typedef bf16_t bf16_lds_t __attribute__((__may_alias__));
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        const int orow = ln & 31, ohalf = ln >> 5;
+        char* mine = out_lds + wave * kOutLds;
+        constexpr int ES = EPI == EPI_STORE_F32 ? 4 : 2;  // bytes per element
+        const size_t row0 = (size_t)(tl.m0 + wr * WM) * ldc;
+        char* base = reinterpret_cast<char*>(C) + (EPI == EPI_STORE_F32 ? tl.split * split_stride + row0 : row0) * ES;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(base, 0, 0x7FFFFFFF, kBufferDword3);
+        constexpr int LR = EPI == EPI_STORE_F32 ? 4 : 2;                 // log2 of the lanes per stored row
+        const int lrow = ln >> LR, n = tl.n0 + (EPI == EPI_STORE_F32 ? wc * WN + (ln & 15) * 4 : wc * (WN / 2) + (ln & 3) * 8);
+        // rows of this lane's runs that exist: run rows below `left` (none past the last column)
+        const int left = n < (EPI == EPI_STORE_F32 ? N : N >> 1) ? M - (tl.m0 + wr * WM) - lrow : 0;
+        const uint32_t out = (uint32_t)((lrow * ldc + n) * ES);
+        auto put = [&](u32x4_t v, int rr) {
+            __builtin_amdgcn_raw_buffer_store_b128(v, rs, rr < left ? out + (uint32_t)(rr * ldc * ES) : kOut, 0, NT ? 2 : 0);
+        };
+        if constexpr (EPI == EPI_STORE_F32) {
+            // rows whose bit 2 is set have their column halves swapped: the two lane halves
+            // (rows 4 apart) write different banks
+            const uint32_t w0 = (ohalf * 4 * 64 + orow + ohalf * 32) * 4, w1 = (ohalf * 4 * 64 + orow + (32 - ohalf * 32)) * 4;
+            const uint32_t r0 = (lrow * 64 + (ln & 15) * 4) * 4, r1 = (lrow * 64 + (((ln & 15) * 4) ^ 32)) * 4;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int hh = 0; hh < 2; ++hh) {  // 16 rows: accumulator registers 8 hh .. 8 hh + 7
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) {
+                        const int at = ((r >> 2) * 8 + (r & 3)) * 256;
+                        *reinterpret_cast<f32_lds_t*>(mine + w0 + at) = acc[i][0][hh * 8 + r];
+                        *reinterpret_cast<f32_lds_t*>(mine + w1 + at) = acc[i][1][hh * 8 + r];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        put(*reinterpret_cast<const u32x4_t*>(mine + (u & 1 ? r1 : r0) + u * 1024), i * 32 + hh * 16 + u * 4);
+                    __builtin_amdgcn_sched_barrier(0);  // one chunk's registers at a time
+                }
+        } else {
+            constexpr int OS = 40;  // 32 columns of h and 8 of padding
+            static_assert(32 * OS * 2 <= kOutLds, "staged rows fit");
+            const uint32_t w0 = (ohalf * 4 * OS + orow) * 2, r0 = (lrow * OS + (ln & 3) * 8) * 2;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    *reinterpret_cast<bf16_lds_t*>(mine + w0 + ((r >> 2) * 8 + (r & 3)) * (OS * 2)) =
+                        f2bf(silu(acc[i][0][r]) * acc[i][1][r]);
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    put(*reinterpret_cast<const u32x4_t*>(mine + r0 + u * 16 * (OS * 2)), i * 32 + u * 16);
+                __builtin_amdgcn_sched_barrier(0);  // one chunk's registers at a time
+            }
+        }
+    };
+
+    clear();
+    wait_vmcnt_lds_reads<0>();
+    __builtin_amdgcn_s_barrier();
+    read(af[0], bfr[0], st0, 0);
+#define DASH_WIDE_SCHED(LOADS)                                                                    \
+    do {                                                                                          \
+        _Pragma("unroll") for (int q_ = 0; q_ < NM; ++q_) {                                       \
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                    \
+            __builtin_amdgcn_sched_group_barrier(0x100, (NR + NM - 1) / NM, 0);                   \
+            if (LOADS) __builtin_amdgcn_sched_group_barrier(0x020, (AI + BI + NM - 1) / NM, 0);   \
+        }                                                                                         \
+        __builtin_amdgcn_sched_barrier(0);                                                        \
+    } while (0)
+    // One k-step (as in gemm_wide_k) that leaves OUTST operations in flight at its wait and
+    // refills its stage by LOAD.
+#define DASH_WIDE_STEP(CUR, NXT, OUTST, LOAD)                                                     \
+    do {                                                                                          \
+        read(af[1], bfr[1], CUR, 1);                                                              \
+        mma(af[0], bfr[0]);                                                                       \
+        DASH_WIDE_SCHED(false);                                                                   \
+        read(af[0], bfr[0], CUR, 2);                                                              \
+        mma(af[1], bfr[1]);                                                                       \
+        DASH_WIDE_SCHED(false);                                                                   \
+        read(af[1], bfr[1], CUR, 3);                                                              \
+        mma(af[0], bfr[0]);                                                                       \
+        DASH_WIDE_SCHED(false);                                                                   \
+        wait_vmcnt_lds_reads<OUTST>();                                                            \
+        __builtin_amdgcn_s_barrier();                                                             \
+        __builtin_amdgcn_sched_barrier(0);                                                        \
+        read(af[0], bfr[0], NXT, 0);                                                              \
+        LOAD;                                                                                     \
+        mma(af[1], bfr[1]);                                                                       \
+        DASH_WIDE_SCHED(true);                                                                    \
+    } while (0)
+    for (;;) {
+        const int n_pad = (n_k + 1) & ~1;
+        t += t_step;
+        const bool more = t < t_end;
+        const WideTile next = more ? tile_at(t) : tile;
+        const int nk_next = more ? steps_of(next) : 0;  // 0: the last loads read out of range
+        const Rows rows_next = rows_of(next);
+        if (n_pad > 2) {
+            // the stores of the tile before may still drain (of the first tile there are none,
+            // and both its first stages had landed before the first read)
+            DASH_WIDE_STEP(st0, st1, kStores, load(st0, rows, 2, n_k));
+            DASH_WIDE_STEP(st1, st0, 0, load(st1, rows, 3, n_k));
+            for (int k = 2; k + 2 < n_pad; k += 2) {
+                DASH_WIDE_STEP(st0, st1, 0, load(st0, rows, k + 2, n_k));
+                DASH_WIDE_STEP(st1, st0, 0, load(st1, rows, k + 3, n_k));
+            }
+        }
+        DASH_WIDE_STEP(st0, st1, 0, load(st0, rows_next, 0, nk_next));
+        DASH_WIDE_STEP(st1, st0, 0, load(st1, rows_next, 1, nk_next));
+        store(tile);
+        if (!more) break;
+        clear();
+        tile = next;
+        n_k = nk_next;
+        rows = rows_next;
+    }
+#undef DASH_WIDE_STEP
+#undef DASH_WIDE_SCHED
+    wait_vmcnt<0>();  // the out-of-range loads past the last tile still write their stages
+}
+
 // Output columns [col0, col1) (SwiGLU: of h; col0 a multiple of the tile's output width).
 template <int WGM, int WGN, int TM, int TN, int EPI, int S = 2>
 hipError_t run_wide_cols(const void* A, const void* W, void* C, int M, int N, int K, int ldc, int nsplit,
@@ -968,8 +1208,33 @@ hipError_t run_wide_cols(const void* A, const void* W, void* C, int M, int N, in
     // rows, 512 -> 505 at 1024; the five partials of the down projection at 16,384 rows 439
     // -> 426.  Smaller outputs are read from that cache next.
     constexpr size_t kCache = (size_t)256 << 20;
+    const bool past_cache = EPI == EPI_STORE_F32 && (size_t)M * (col1 - col0) * nsplit * 4 > kCache;
+    // From two rounds on the 256x256 tile runs in work-groups that stay, where the output can be
+    // written in 16-byte runs: gate/up 1.5B 729 -> 687 us at 16,384 rows and 0.5B 73.7 -> 68.5
+    // at 4,206, down 1.5B 262 -> 247 at 10,240, LM head 1.5B 3737 -> 3667 at 8,192 and 0.5B 956 ->
+    // 924 at 3,066 (K = 896; 628 against 661 at 2,048).  Work-groups that stay can't hand the
+    // tiles of a last round that is mostly empty to the CUs that are ahead, and where the steps
+    // of a tile are many that costs more than the seams save: LM head 1.5B at 1,024 rows (9.28
+    // rounds) 514 against 500, at 1,792 (16.24) 865 against 854, but at 1,280 (11.6) 606 against
+    // 613 after.  So from 1,024 of K on a launch of under 32 rounds goes there with a third of
+    // its last round filled.
+    constexpr int V = EPI == EPI_SWIGLU ? 8 : 4;  // elements per run
+    if constexpr (WGM == 2 && WGN == 4 && TM == 4 && TN == 2 && S == 2 && EPI != EPI_QKV_ROPE) {
+        const bool seams_pay = kps < 1024 || blocks >= 32 * 256 || (blocks - 1) % 256 >= 85;
+        if (blocks >= 512 && seams_pay && ldc % V == 0 && (EPI == EPI_SWIGLU ? N / 2 : N) % V == 0 &&
+            split_stride % V == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0 && (size_t)BM * ldc * 4 < (1u << 31)) {
+            auto run = [&](auto nt) {
+                gemm_wide_persist_k<EPI, decltype(nt)::value><<<256, 512, 0, st>>>(
+                    (const bf16_t*)A, (const bf16_t*)W, C, M, N, K, ldc, m_tiles, n_tiles, col0 / tn, gm, kps, split_stride, blocks);
+                return hipGetLastError();
+            };
+            if constexpr (EPI == EPI_STORE_F32)
+                if (past_cache) return run(std::true_type{});
+            return run(std::false_type{});
+        }
+    }
     if constexpr (EPI == EPI_STORE_F32)
-        if ((size_t)M * (col1 - col0) * nsplit * 4 > kCache) {
+        if (past_cache) {
             gemm_wide_k<WGM, WGN, TM, TN, EPI, S, true><<<blocks, 64 * WGM * WGN, 0, st>>>(
                 (const bf16_t*)A, (const bf16_t*)W, C, M, N, K, ldc, m_tiles, n_tiles, col0 / tn, gm, kps, split_stride, qa);
             return hipGetLastError();

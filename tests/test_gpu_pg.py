@@ -107,13 +107,17 @@ def test_pg_loss_edge_cases():
 # vocabularies past the LM head's tile width
 WIDE_A = synth.Shape("wide-hd64", 2, 320, 8, 2, 64, 448, 8200, 1e6, synth.DT_BF16)
 WIDE_B = synth.Shape("wide-hd128", 1, 192, 6, 2, 128, 576, 8193, 1e6, synth.DT_BF16)
+# enough tiles for the work-groups that stay, odd step counts (5, 9) beside even ones (a last split of 2)
+WIDE_D = synth.Shape("wide-persistent", 1, 320, 4, 2, 64, 4160, 33000, 1e6, synth.DT_BF16)
+WIDE_E = synth.Shape("wide-persistent-k64", 1, 64, 6, 1, 64, 1024, 300, 1e6, synth.DT_BF16)  # one step a tile
 WIDE_C = synth.Shape("wide-k64", 1, 64, 6, 1, 64, 64, 300, 1e6, synth.DT_BF16)
 
 
 @pytest.mark.parametrize("shape,n,P,L_", [(WIDE_A, 8, 600, 701),    # 128x128 QKV tiles, rows off the pages
                                           (WIDE_A, 16, 650, 704),   # 256x256 QKV tiles, whole pages of keys
                                           (WIDE_B, 5, 640, 701), (WIDE_B, 10, 660, 701),
-                                          (WIDE_C, 65, 500, 512)])
+                                          (WIDE_C, 65, 500, 512), (WIDE_D, 16, 636, 704), (WIDE_D, 15, 632, 701),
+                                          (WIDE_E, 65, 500, 512)])
 def test_wide_tiles_bit_identical_to_small_batches(shape, n, P, L_):
     """Many sequences in one forward pass (the wide GEMM tiles, their last row and column tiles
     partly empty, the QKV projection's RoPE and KV append from the accumulators) give the bits of
