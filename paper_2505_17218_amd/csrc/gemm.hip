@@ -756,7 +756,7 @@ DASH_DEV void wide_qkv_epilogue(const f32x16_t (&acc)[TM][4], const QkvRopeArgs&
     }
 }
 
-template <int WGM, int WGN, int TM, int TN, int EPI, int S, bool NT>
+template <int WGM, int WGN, int TM, int TN, int EPI, int S, bool NT, bool SUM = false>
 __global__ void __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(2)))
 gemm_wide_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __restrict__ C, int M, int N, int K,
             int ldc, int m_tiles, int n_tiles, int nt0, int gm, int kps, size_t split_stride, QkvRopeArgs qa) {
@@ -779,7 +779,7 @@ gemm_wide_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __
     wide_tile_of(w - split * tiles, m_tiles, n_tiles, gm, mt, nt);
     nt += nt0;  // a launch may cover the column tiles from nt0 on
     const int m0 = mt * BM;
-    const int k_begin = split * kps, k_end = min(K, k_begin + kps);
+    const int k_begin = split * kps, k_end = SUM ? K : min(K, k_begin + kps);
     const int n_k = (k_end - k_begin) / kBK;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -830,6 +830,31 @@ gemm_wide_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
+    // SUM: every kps of K the accumulators are a partial, added to the sum of those before it
+    // (0 + p0 + p1 ..., the order and so the bits of the kernel that reads separate partials:
+    // an accumulator is never -0).  Two accumulator sets fit beside the fragments for 64 x 64 of
+    // output a wave, not for 128 x 64: 256x192 and 192x256 tiles spill and take 1.3-2.4 times as long.
+    [[maybe_unused]] f32x16_t sum[SUM ? TM : 1][SUM ? TN : 1];
+    [[maybe_unused]] int fold_at = kps / kBK;
+    if constexpr (SUM)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sum[i][j][r] = 0.f;
+    [[maybe_unused]] auto fold = [&](bool last) {
+        if constexpr (SUM)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        sum[i][j][r] += acc[i][j][r];
+                        acc[i][j][r] = last ? sum[i][j][r] : 0.f;
+                    }
+    };
     const int frow = lane & 31, fhalf = lane >> 5;
     bf16x8_t af[2][TM], bfr[2][TN];
     auto read = [&](bf16x8_t (&a)[TM], bf16x8_t (&b)[TN], const LdsStage<BM, BN>& sg, int ks) {
@@ -863,6 +888,11 @@ gemm_wide_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __
     } while (0)
 #define DASH_WIDE_STEP(CUR, NXT, KK)                                                              \
     do {                                                                                          \
+        if constexpr (SUM)                                                                        \
+            if ((KK) == fold_at) {                                                                \
+                fold(false);                                                                      \
+                fold_at += kps / kBK;                                                             \
+            }                                                                                     \
         read(af[1], bfr[1], CUR, 1);                                                              \
         mma(af[0], bfr[0]);                                                                       \
         DASH_WIDE_SCHED(false);                                                                   \
@@ -911,6 +941,7 @@ gemm_wide_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __
     // the loads past the end still write their stages, and the last reads their registers
     wait_vmcnt_lds_reads<0>();
     __syncthreads();
+    if constexpr (SUM) fold(true);
     if constexpr (EPI == EPI_QKV_ROPE) {
         static_assert(NW / 2 * 32 * kQkvRow <= (BM + BN) * kBK, "staged rows fit the stages");
         bf16_t* hs = (wave < NW / 2 ? st0.a : st1.a) + wave % (NW / 2) * (32 * kQkvRow);
@@ -1249,6 +1280,20 @@ hipError_t run_wide(const void* A, const void* W, void* C, int M, int N, int K, 
                     size_t split_stride, hipStream_t st, const QkvRopeArgs& qa = QkvRopeArgs{}) {
     return run_wide_cols<WGM, WGN, TM, TN, EPI, S>(A, W, C, M, N, K, ldc, nsplit, split_stride, 0,
                                                    EPI == EPI_SWIGLU ? N / 2 : N, st, qa);
+}
+
+// All nsplit partials of a tile by one work-group, added in registers in split order.
+template <int WGM, int WGN, int TM, int TN, int S>
+hipError_t run_wide_sum(const void* A, const void* W, void* C, int M, int N, int K, int nsplit, hipStream_t st) {
+    constexpr int BM = WGM * TM * 32, BN = WGN * TN * 32;
+    const int m_tiles = (M + BM - 1) / BM, n_tiles = (N + BN - 1) / BN;
+    const int kps = ((K + nsplit - 1) / nsplit + kBK - 1) / kBK * kBK;
+    if ((K + kps - 1) / kps != nsplit) return hipErrorInvalidValue;
+    if (K % kBK || (size_t)M * K * 2 >= (1u << 31) || (size_t)N * K * 2 >= (1u << 31)) return hipErrorInvalidValue;
+    // tile order: 4 rows of tiles per block (8 and 12 measured: within 3% either way)
+    gemm_wide_k<WGM, WGN, TM, TN, EPI_STORE_F32, S, false, true><<<m_tiles * n_tiles, 64 * WGM * WGN, 0, st>>>(
+        (const bf16_t*)A, (const bf16_t*)W, C, M, N, K, N, m_tiles, n_tiles, 0, 4, kps, 0, QkvRopeArgs{});
+    return hipGetLastError();
 }
 
 // ---- small batches ---------------------------------------------------------------
@@ -1600,6 +1645,39 @@ int gemm_pick_splits(int dtype, int epi, int N, int K) {
     int kps = (K + s - 1) / s;
     kps = (kps + kBK - 1) / kBK * kBK;
     return (K + kps - 1) / kps;
+}
+
+// Tiles of 256x128, or of 128x256 where those take fewer rounds (or as many, past one).
+static bool sum_tall(int M, int N, long* tiles) {
+    const long tall = (long)((M + 255) / 256) * ((N + 127) / 128), flat = (long)((M + 127) / 128) * ((N + 255) / 256);
+    const long rt = (tall + 255) / 256, rf = (flat + 255) / 256;
+    const bool use_tall = rt < rf || (rt == rf && rt == 1);
+    *tiles = use_tall ? tall : flat;
+    return use_tall;
+}
+
+// What it saves: nsplit - 1 partials written and read back, about 26 us a full round of 1.5B
+// tiles.  What it costs: a tile takes the whole of K, so a last round that is partly empty is
+// as many times longer as there are splits.  So it pays by empty tiles x steps of K against
+// tiles x (nsplit - 1): up to a ratio of 12 (20 within one round, whose empty CUs leave the
+// others the memory and the clock).  us with the norm that reads the output, split / summed,
+// at (rows, ratio): 1.5B 16,384 (0) 535 / 454, 10,843 (0) 393 / 302, 8,155 (11.7) 270 / 262,
+// 11,867 (13.2) 398 / 396, 4,059 (11.7) 138 / 124; 3B 4,059 (0) 191 / 173, 6,875 (10.5) 377 /
+// 341, 3,035 (19) 158 / 155, 6,107 (19) 294 / 315, 2,523 (35) 145 / 149; 0.5B 16,347 (0) 322 /
+// 181, 5,211 (8) 98 / 66; 3584 x 18,944 in two splits 3,931 (42) 504 / 540.
+bool gemm_sum_pays(int dtype, int M, int N, int K, int nsplit) {
+    if (dtype != 1 || nsplit < 2 || M <= 1024 || K % kBK) return false;
+    if ((size_t)M * K * 2 >= (1u << 31) || (size_t)N * K * 2 >= (1u << 31)) return false;
+    long tiles;
+    sum_tall(M, N, &tiles);
+    const long empty = (256 - tiles % 256) % 256;
+    return empty * (K / kBK) <= (tiles <= 256 ? 20 : 12) * (nsplit - 1) * tiles;
+}
+
+hipError_t launch_gemm_sum(const void* A, const void* W, void* C, int M, int N, int K, int nsplit, hipStream_t st) {
+    long tiles;
+    if (sum_tall(M, N, &tiles)) return run_wide_sum<4, 2, 2, 2, 3>(A, W, C, M, N, K, nsplit, st);
+    return run_wide_sum<2, 4, 2, 2, 3>(A, W, C, M, N, K, nsplit, st);
 }
 
 bool gemm_qkv_fusable(int dtype, int n_heads, int n_kv, int head_dim) {

@@ -64,6 +64,10 @@ hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C
                        int nsplit, size_t split_stride, hipStream_t st);
 // Split-K count for a weight of N x K (independent of M: results are batch-invariant).
 int gemm_pick_splits(int dtype, int epi, int N, int K);
+// C = the sum of launch_gemm's nsplit partials in split order, bit for bit, row stride N; where
+// gemm_sum_pays says so it is faster than leaving the partials to the kernel that reads them.
+bool gemm_sum_pays(int dtype, int M, int N, int K, int nsplit);
+hipError_t launch_gemm_sum(const void* A, const void* W, void* C, int M, int N, int K, int nsplit, hipStream_t st);
 // QKV projection with bias, RoPE and the KV append in the epilogue: the same values
 // as launch_gemm(EPI_STORE_F32, nsplit 1) followed by launch_qkv_rope_append, bit for
 // bit.  Available for bf16 models whose q and kv column ranges are multiples of 128

@@ -626,6 +626,8 @@ int run_layers(dash_model* m, dash_kv* kv, const Ws& w, int rows, const int32_t*
     const int sq = gemm_pick_splits(dt, EPI_STORE_F32, qr, d.d_model);
     const int so = gemm_pick_splits(dt, EPI_STORE_F32, d.d_model, hq);
     const int sd = gemm_pick_splits(dt, EPI_STORE_F32, d.d_model, d.d_ff);
+    const bool sum_down = gemm_sum_pays(dt, rows, d.d_model, d.d_ff, sd);
+    const int left = sum_down ? 1 : sd;  // partials that the down projection leaves for the norm
     const bool fuse_qkv = gemm_qkv_fusable(dt, d.n_heads, d.n_kv_heads, d.head_dim) && gemm_qkv_fuse_pays(rows, qr);
     // Prefix-shared decode attention keeps its per-row states in the fp32 QKV buffer, dead
     // while attention runs (the fused projection never writes it; the unfused one's output
@@ -651,7 +653,7 @@ int run_layers(dash_model* m, dash_kv* kv, const Ws& w, int rows, const int32_t*
         cur_layer = l;
         if (l > 0) {
             ProfScope ps(cls(DASH_K_NORM), st);
-            DASH_HIP(launch_add_rmsnorm(dt, w.x, w.delta, sd, (size_t)rows * d.d_model, m->lw(l, 0), w.y, nullptr, rows,
+            DASH_HIP(launch_add_rmsnorm(dt, w.x, w.delta, left, (size_t)rows * d.d_model, m->lw(l, 0), w.y, nullptr, rows,
                                         d.d_model, d.rms_eps, 1, st));
         }
         if (fuse_qkv) {  // projection, bias, RoPE and the KV append in one kernel
@@ -705,11 +707,14 @@ int run_layers(dash_model* m, dash_kv* kv, const Ws& w, int rows, const int32_t*
         }
         {
             ProfScope ps(cls(DASH_K_GEMM_DOWN), st);
-            DASH_HIP(launch_gemm(dt, EPI_STORE_F32, w.h, m->lw(l, 6), w.delta, rows, d.d_model, d.d_ff, d.d_model, sd,
-                                 (size_t)rows * d.d_model, st));
+            if (sum_down)
+                DASH_HIP(launch_gemm_sum(w.h, m->lw(l, 6), w.delta, rows, d.d_model, d.d_ff, sd, st));
+            else
+                DASH_HIP(launch_gemm(dt, EPI_STORE_F32, w.h, m->lw(l, 6), w.delta, rows, d.d_model, d.d_ff, d.d_model, sd,
+                                     (size_t)rows * d.d_model, st));
         }
     }
-    *last_split = sd;
+    *last_split = left;
     return DASH_OK;
 }
 

@@ -107,9 +107,12 @@ def test_pg_loss_edge_cases():
 # vocabularies past the LM head's tile width
 WIDE_A = synth.Shape("wide-hd64", 2, 320, 8, 2, 64, 448, 8200, 1e6, synth.DT_BF16)
 WIDE_B = synth.Shape("wide-hd128", 1, 192, 6, 2, 128, 576, 8193, 1e6, synth.DT_BF16)
-# enough tiles for the work-groups that stay, odd step counts (5, 9) beside even ones (a last split of 2)
+# enough tiles for the work-groups that stay, an odd step count (5); the down projection's eight splits (nine steps, the
+# last two) summed in one work-group
 WIDE_D = synth.Shape("wide-persistent", 1, 320, 4, 2, 64, 4160, 33000, 1e6, synth.DT_BF16)
 WIDE_E = synth.Shape("wide-persistent-k64", 1, 64, 6, 1, 64, 1024, 300, 1e6, synth.DT_BF16)  # one step a tile
+# five splits: at 5440 rows left as partials by the work-groups that stay, at 6375 summed on 128x256 tiles
+WIDE_F = synth.Shape("wide-five-splits", 1, 1536, 4, 2, 64, 4160, 300, 1e6, synth.DT_BF16)
 WIDE_C = synth.Shape("wide-k64", 1, 64, 6, 1, 64, 64, 300, 1e6, synth.DT_BF16)
 
 
@@ -117,7 +120,7 @@ WIDE_C = synth.Shape("wide-k64", 1, 64, 6, 1, 64, 64, 300, 1e6, synth.DT_BF16)
                                           (WIDE_A, 16, 650, 704),   # 256x256 QKV tiles, whole pages of keys
                                           (WIDE_B, 5, 640, 701), (WIDE_B, 10, 660, 701),
                                           (WIDE_C, 65, 500, 512), (WIDE_D, 16, 636, 704), (WIDE_D, 15, 632, 701),
-                                          (WIDE_E, 65, 500, 512)])
+                                          (WIDE_E, 65, 500, 512), (WIDE_F, 8, 650, 680), (WIDE_F, 15, 400, 425)])
 def test_wide_tiles_bit_identical_to_small_batches(shape, n, P, L_):
     """Many sequences in one forward pass (the wide GEMM tiles, their last row and column tiles
     partly empty, the QKV projection's RoPE and KV append from the accumulators) give the bits of
