@@ -1832,11 +1832,10 @@ hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C
         if (M <= 256 && K < 4096)
             return run_bf16<64, 32, 2, 1, 4, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
         // Larger batches: the largest tile that still gives the launch enough work-groups.
-        // Measured crossovers on the 0.5B, 1.5B and 3B shapes: the split down projection
-        // 64x64 up to 384 rows (12-19% faster than 64x32 there), the direct-to-LDS 128x128 tiles up to 640, 128x256 up to 1024,
-        // 256x256 past that (12-18% faster from 1536 rows); QKV / O 64x64 three k-steps ahead up to 512 rows (10-15% faster than two),
-        // 64x64 up to 1024, 128x128 up to 4096 (4-30% faster from 1536), 256x256 past that
-        // (15-26% faster at 8192-16384).
+        // Measured crossovers on the 0.5B, 1.5B and 3B shapes: the split down projection 64x64 up
+        // to 384 rows (12-19% faster than 64x32 there), the direct-to-LDS 128x128 tiles up to
+        // 640, 128x256 up to 1024, 256x256 past that (12-18% faster from 1536 rows); unsplit
+        // projections 256x256 past 4096 rows (15-26% faster than 128x128 at 8192-16384).
         if (K >= 4096) {
             if (M <= 384)
                 return run_bf16<64, 64, 2, 2, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
@@ -1851,12 +1850,6 @@ hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C
                 return run_bf16<128, 256, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             return run_wide<2, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
         }
-        if (M <= 512)
-            return run_bf16<64, 64, 2, 2, 3, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
-        if (M <= 1024)  // decode QKV / O: unsplit, small tiles fill the GPU
-            return run_bf16<64, 64, 2, 2, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
-        if (M <= 4096)
-            return run_bf16<128, 128, 4, 2, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
         return run_wide<2, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
     }
     if (nsplit != 1) return hipErrorInvalidValue;
