@@ -29,6 +29,7 @@
 // wave-wide maximum, and sixteen waves each raised their own), a bound test per entry, an
 // online sum with a select per entry and two-operand xors in Philox.
 #include <cstring>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
@@ -431,6 +432,41 @@ DASH_DEV void kl_push(KlAcc& s, float x, float y) {
     }
 }
 
+// Four finite pairs of logits into both sides: one rescale of a side to its new maximum, then the
+// four terms without a branch.
+DASH_DEV void kl_raise(KlAcc& s, const float (&x)[4]) {
+    const float m = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+    if (!(m > s.m)) return;
+    const double c = (double)__expf(s.m - m);  // 0 from m = -inf
+    s.z *= c;
+    s.w *= c;
+    s.m = m;
+}
+
+// A sum of the eight that is finite shows that all are; a wave with any other takes them one by one.
+DASH_DEV void kl_push4(KlAcc& sa, KlAcc& sb, const float (&a)[4], const float (&b)[4]) {
+    const float t = ((a[0] + a[1]) + (a[2] + a[3])) + ((b[0] + b[1]) + (b[2] + b[3]));
+    if (__any(!(fabsf(t) < INFINITY))) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            kl_push(sa, a[j], b[j]);
+            kl_push(sb, b[j], a[j]);
+        }
+        return;
+    }
+    kl_raise(sa, a);
+    kl_raise(sb, b);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const double d = (double)a[j] - (double)b[j];
+        const double ea = (double)__expf(a[j] - sa.m), eb = (double)__expf(b[j] - sb.m);
+        sa.z += ea;
+        sa.w = __builtin_fma(ea, d, sa.w);
+        sb.z += eb;
+        sb.w = __builtin_fma(eb, -d, sb.w);
+    }
+}
+
 DASH_DEV void kl_merge(KlAcc& s, float om, double oz, double ow, int oinf) {
     s.inf |= oinf;
     const float m = fmaxf(s.m, om);
@@ -448,13 +484,18 @@ DASH_DEV double kl_final(const KlAcc& x, const KlAcc& y) {
 
 // LP: also the log-probability of a given token under softmax(theta), in logprob_gather_k's
 // order and bits: thread u stands for that kernel's threads u, u + 256, u + 512 and u + 768,
-// each with its own running (max, sum).  One read of the policy's logits instead of two:
-// 3066 rows of 151,936 take 780 us against 672 + 370 for the two kernels.
-template <bool LP>
+// each with its own running (max, sum).  One read of the policy's logits instead of two.
+//
+// What bounds it: reading both rows, and close behind it the fp64 sums (two exponentials and eight
+// conversions and fp64 operations per entry).  The next group's loads are in flight while a
+// group is summed, and a group of finite entries takes one rescale per side and no branch per
+// entry: 2048 rows of 151,936 421 -> 368 us (6.8 TB/s), against a load, a wait for it and two
+// branches per entry and side.
+template <bool LP, bool VEC4>
 __global__ void __launch_bounds__(kKlThreads)
 kl_rows_k(const float* __restrict__ theta, const float* __restrict__ base, int64_t ld, int vocab,
-          float* __restrict__ kl, float* __restrict__ kl_rev, int vec4, const int32_t* __restrict__ tokens, int per,
-          int stride, int off, float* __restrict__ lp_out) {
+          float* __restrict__ kl, float* __restrict__ kl_rev, const int32_t* __restrict__ tokens, int per, int stride,
+          int off, float* __restrict__ lp_out) {
     constexpr int kVirt = kThreads / kKlThreads;  // gather threads per thread
     [[maybe_unused]] __shared__ float lse_m[LP ? kThreads / 64 : 1], lse_z[LP ? kThreads / 64 : 1];
     [[maybe_unused]] float mx[kVirt], z[kVirt];
@@ -471,40 +512,48 @@ kl_rows_k(const float* __restrict__ theta, const float* __restrict__ base, int64
     const float* rb = base + (int64_t)r * ld;
     KlAcc sa{-INFINITY, 0.0, 0.0, 0}, sb{-INFINITY, 0.0, 0.0, 0};
     const int n4 = (vocab + 3) >> 2;
-    auto group = [&](int g, float (&a)[4], float (&b)[4]) {
-        if (vec4 && 4 * g + 3 < vocab) {
-            const float4 va = load_stream4(ra + 4 * g);
-            const float4 vb = load_stream4(rb + 4 * g);
+    const int nf = vocab >> 2;  // whole groups
+    // The same loads for every lane and group: past the row's end they repeat its last group
+    // (word), and the entries are masked when they are used.
+    auto fetch = [&](int g, float (&a)[4], float (&b)[4]) {
+        if constexpr (VEC4) {
+            const int at = 4 * min(g, nf - 1);
+            const float4 va = load_stream4(ra + at);
+            const float4 vb = load_stream4(rb + at);
             a[0] = va.x; a[1] = va.y; a[2] = va.z; a[3] = va.w;
             b[0] = vb.x; b[1] = vb.y; b[2] = vb.z; b[3] = vb.w;
         } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {  // entries past the vocabulary have no mass on either side
-                a[j] = 4 * g + j < vocab ? ra[4 * g + j] : -INFINITY;
-                b[j] = 4 * g + j < vocab ? rb[4 * g + j] : -INFINITY;
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t at = min(4u * min(g, n4 - 1) + j, vocab - 1u);
+                a[j] = ra[at];
+                b[j] = rb[at];
             }
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            kl_push(sa, a[j], b[j]);
-            kl_push(sb, b[j], a[j]);
         }
     };
-    if constexpr (LP) {
-        for (int g0 = threadIdx.x; g0 < n4; g0 += kThreads) {
+    float na[4], nb[4];
+    fetch(threadIdx.x, na, nb);
+    for (int g0 = 0; g0 < n4; g0 += kThreads) {
 #pragma unroll
-            for (int v = 0; v < kVirt; ++v) {
-                const int g = g0 + v * kKlThreads;
-                if (g >= n4) break;
-                float a[4], b[4];
-                group(g, a, b);
-                lse_push4(mx[v], z[v], a);
+        for (int v = 0; v < kVirt; ++v) {
+            if (g0 + v * kKlThreads >= n4) break;
+            const int g = g0 + v * kKlThreads + threadIdx.x;
+            float a[4] = {na[0], na[1], na[2], na[3]}, b[4] = {nb[0], nb[1], nb[2], nb[3]};
+            fetch(g + kKlThreads, na, nb);
+            if (g0 + (v + 1) * kKlThreads > nf) {  // the last groups: entries past the vocabulary have no mass
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const bool in = 4u * g + j < (uint32_t)vocab;
+                    if (VEC4 && in && g >= nf) {
+                        a[j] = ra[4 * g + j];
+                        b[j] = rb[4 * g + j];
+                    }
+                    a[j] = in ? a[j] : -INFINITY;
+                    b[j] = in ? b[j] : -INFINITY;
+                }
             }
-        }
-    } else {
-        for (int g = threadIdx.x; g < n4; g += kKlThreads) {
-            float a[4], b[4];
-            group(g, a, b);
+            kl_push4(sa, sb, a, b);
+            if constexpr (LP) lse_push4(mx[v], z[v], a);
         }
     }
     const int w = threadIdx.x >> 6;
@@ -557,14 +606,15 @@ hipError_t launch_logits_kl(const float* theta, const float* base, int64_t ld, i
                             float* lp_out) {
     if (rows <= 0) return hipSuccess;
     if (vocab < 1 || ld < vocab || (lp_out && (!tokens || per < 1))) return hipErrorInvalidValue;
-    const int vec4 =
-        ((ld & 3) == 0 && ((uintptr_t)theta & 15) == 0 && ((uintptr_t)base & 15) == 0) ? 1 : 0;
-    if (lp_out)
-        kl_rows_k<true><<<rows, kKlThreads, 0, st>>>(theta, base, ld, vocab, kl, kl_rev, vec4, tokens, per, stride, off,
-                                                     lp_out);
-    else
-        kl_rows_k<false><<<rows, kKlThreads, 0, st>>>(theta, base, ld, vocab, kl, kl_rev, vec4, nullptr, 1, 0, 0,
-                                                      nullptr);
+    const bool vec4 = (ld & 3) == 0 && ((uintptr_t)theta & 15) == 0 && ((uintptr_t)base & 15) == 0 && vocab >= 4;
+    auto run = [&](auto lp, auto vec) {
+        kl_rows_k<decltype(lp)::value, decltype(vec)::value>
+            <<<rows, kKlThreads, 0, st>>>(theta, base, ld, vocab, kl, kl_rev, tokens, per, stride, off, lp_out);
+    };
+    if (lp_out && vec4) run(std::true_type{}, std::true_type{});
+    else if (lp_out) run(std::true_type{}, std::false_type{});
+    else if (vec4) run(std::false_type{}, std::true_type{});
+    else run(std::false_type{}, std::false_type{});
     return hipGetLastError();
 }
 

@@ -217,6 +217,47 @@ def test_policy_loss_edge_cases():
     assert abs(float(loss.item()) - 0.3125) < 1e-6
 
 
+@pytest.mark.parametrize("V", [1, 3, 4, 7, 1020, 1024, 1027, 1028, 4095, 4100, 5125])
+@pytest.mark.parametrize("pad", [0, 1, 4])
+def test_logits_kl_group_edges(V, pad):
+    """Vocabularies around a group of four, a pass of the workgroup (1024 entries) and the four
+    passes of an unrolled step, rows aligned and not, with a masked entry, a NaN and an infinity in
+    rows of their own (waves that take their entries one by one)."""
+    rows, ld = 6, V + pad
+    theta = np.full((rows, ld), np.nan, np.float32)
+    base = np.full((rows, ld), np.nan, np.float32)  # the padding is never used
+    theta[:, :V] = synth.make_logits(rows, V, seed=35, scale=4.0)
+    base[:, :V] = synth.make_logits(rows, V, seed=36, scale=4.0)
+    if V > 1:
+        theta[1, V // 2] = base[1, V // 2] = -np.inf
+        theta[2, V - 1] = -np.inf
+    base[4, 0] = np.nan
+    theta[5, V - 1] = np.inf
+    t, b = torch.from_numpy(theta).cuda(), torch.from_numpy(base).cuda()
+    kl, kl_rev = (x.cpu().numpy() for x in engine.logits_kl(t[:, :V], b[:, :V]))
+    ref = opol.kl_rows(theta[:4, :V].astype(np.float64), base[:4, :V].astype(np.float64))
+    for r in range(4):
+        for got, want in ((kl[r], ref[0][r]), (kl_rev[r], ref[1][r])):
+            if np.isinf(want):
+                assert got == want
+            else:
+                assert abs(got - want) <= _kl_row_tol(theta[r, :V], base[r, :V], want), (r, got, want)
+    assert np.isnan(kl[4:]).all() and np.isnan(kl_rev[4:]).all()
+
+
+@pytest.mark.parametrize("vocab", [4104, 5122])
+def test_teacher_forced_kl_logprobs_past_one_pass(vocab):
+    """The log-probs from the row-KL kernel's pass, over more groups than one unrolled step of its
+    threads (rows aligned and not), have the bits of the log-prob gather."""
+    shape = synth.Shape("kl-vocab", 1, 128, 2, 1, 64, 128, vocab, 1e6, synth.DT_BF16)
+    model, base = (engine.Model(shape, synth.make_weights(shape, s)) for s in (43, 44))
+    _, _, seqs = _seqs(shape, 3, 5, 12, 43)
+    kv, d_seqs = make_kv(model, 32, 3, 17), dev_i32(seqs)
+    lp, _, _ = engine.teacher_forced_kl(model, base, kv, d_seqs, 5)
+    want = engine.teacher_forced_logprobs(model, kv, d_seqs, 5)
+    np.testing.assert_array_equal(lp.cpu().numpy().view(np.uint32), want.cpu().numpy().view(np.uint32))
+
+
 @pytest.mark.parametrize("N,T", [(3, 1), (1500, 513)])
 def test_loss_routes_bit_identical(N, T):
     """The row sums go through stats, through the sequence log-probs, or stay inside the one
