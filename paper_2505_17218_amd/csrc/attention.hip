@@ -562,6 +562,55 @@ prefill_attn_bf16_k(const bf16_t* __restrict__ q, const int32_t* __restrict__ sl
     if (valid) attn_store<HD>(st, l, o + (row * n_heads + h) * HD, grp);
 }
 
+// The same with a wave per (prompt, query head, 16 consecutive query positions) that reads its K/V
+// blocks into registers: short prompts and few of them, where the work-groups of the kernel above
+// leave CUs idle while their waves share a SIMD and wait for each other's copies.
+template <int HD>
+__global__ void __launch_bounds__(64) prefill_attn_wave_k(const bf16_t* __restrict__ q, const int32_t* __restrict__ slot,
+                                                          const int32_t* __restrict__ page_table,
+                                                          const bf16_t* __restrict__ pool, KVGeom g, int layer,
+                                                          int n_heads, int P, bf16_t* __restrict__ o, float scale_log2) {
+    constexpr int NC = HD / 32;
+    const int lane = threadIdx.x, col = lane & 15, grp = lane >> 4;
+    const int qblocks = (P + 15) >> 4;
+    const int prompt = blockIdx.x / qblocks, q0 = (blockIdx.x % qblocks) * 16;
+    const int h = blockIdx.y, kvh = h / (n_heads / g.n_kv);
+    const int qp = q0 + col;                 // this column's query position
+    const bool valid = qp < P;
+    const size_t row = (size_t)prompt * P + (valid ? qp : q0);
+    const int sl = slot[(size_t)prompt * P];
+    const int last = min(P, q0 + 16);        // keys < last are written
+    bf16x8_t qf[NC];
+    {
+        const bf16_t* qrow = q + (row * n_heads + h) * HD;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) qf[c] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(qrow + c * 32 + grp * 8));
+    }
+    AttnState<HD> st;
+    attn_init(st);
+    const int lim = valid ? qp + 1 : 1;
+    const int nblk = (last + 31) >> 5;
+    KVRegs<HD> r[2];
+    auto fetch = [&](KVRegs<HD>& dst, int b) {
+        const int key0 = b << 5;
+        int page = kv_page_of(g, page_table, sl, key0);
+        const bool ok = page >= 0;
+        page = ok ? page : 0;
+        load_kv<HD, kKvReuse>(dst, pool + kv_block(g, layer, page, kvh, 0), pool + kv_block(g, layer, page, kvh, 1),
+                              g.page_size, key0 % g.page_size, ok, col, grp);
+    };
+    fetch(r[0], 0);
+    for (int b = 0; b < nblk; b += 2) {
+        fetch(r[1], min(b + 1, nblk - 1));
+        attn_block<HD>(st, r[0], qf, b << 5, lim, last, scale_log2, grp);
+        if (b + 1 >= nblk) break;
+        fetch(r[0], min(b + 2, nblk - 1));
+        attn_block<HD>(st, r[1], qf, (b + 1) << 5, lim, last, scale_log2, grp);
+    }
+    const float l = attn_denominator(st);
+    if (valid) attn_store<HD>(st, l, o + (row * n_heads + h) * HD, grp);
+}
+
 // Merge the context splits of rows that have more than one, in split order:
 // o = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.  One wave per (row, head), a
 // lane per output dim (two for hd = 128).  Up to MS splits every load is issued
@@ -813,6 +862,22 @@ hipError_t launch_prefill_attention(int dtype, const void* q, const int32_t* pos
         const int prompts = rows / prompt_len, qtiles = (prompt_len + 16 * nq - 1) / (16 * nq);
         dim3 grid(prompts * qtiles, g.n_kv * chunks);
         const float sl2 = scale * kLog2e;
+        // Under three quarters of a work-group per CU a wave per (head, 16 positions) is faster.  us,
+        // wave / group of heads (0.5B, 1.5B, 3B shapes): 1 x 48 (6 work-groups) 4.3 / 5.7, 5.2 / 7.2,
+        // 4.9 / 8.1; 2 x 165 (44) 7.0 / 8.9, 8.5 / 10.6, 8.1 / 11.0; 4 x 333 (168) 11.5 / 12.6,
+        // 15.6 / 16.0, 16.8 / 17.6; 3 x 700 (264) 23.9 / 21.2, 29.5 / 27.4, 32.2 / 29.6; 8 x 700 (704)
+        // 41.4 / 37.5, 61.7 / 46.6, 79.3 / 54.2.  (The group kernel with two waves a work-group:
+        // 7.4, 10.0 and 9.1 at 2 x 165.)
+        if ((long)grid.x * grid.y < 192 && (g.head_dim == 128 || g.head_dim == 64)) {
+            const dim3 wgrid(prompts * ((prompt_len + 15) / 16), n_heads);
+            if (g.head_dim == 128)
+                prefill_attn_wave_k<128><<<wgrid, 64, 0, st>>>((const bf16_t*)q, slot, page_table, (const bf16_t*)pool, g,
+                                                               layer, n_heads, prompt_len, (bf16_t*)o, sl2);
+            else
+                prefill_attn_wave_k<64><<<wgrid, 64, 0, st>>>((const bf16_t*)q, slot, page_table, (const bf16_t*)pool, g,
+                                                              layer, n_heads, prompt_len, (bf16_t*)o, sl2);
+            return hipGetLastError();
+        }
 #define DASH_PREFILL(HD, U)                                                                                     \
     prefill_attn_bf16_k<HD, U><<<grid, 64 * nw, 0, st>>>((const bf16_t*)q, slot, page_table, (const bf16_t*)pool, \
                                                          g, layer, n_heads, prompt_len, (bf16_t*)o, sl2, wg_heads, nq)

@@ -672,3 +672,19 @@ def test_prefill_attention_head_groups(hd, n_heads, n_kv):
         for n in range(2):
             want = om.rollout_logits(shape_dict(shape), w, prompts[n], np.zeros(1, np.int32))[0]
             assert np.abs(got[n] - want).max() <= 3e-2, (P, n)
+
+
+@pytest.mark.parametrize("hd,n_heads,n_kv", [(64, 2, 2), (64, 4, 2), (64, 6, 2), (64, 7, 1), (64, 9, 1), (64, 16, 1),
+                                             (128, 1, 1), (128, 2, 1), (128, 3, 1), (128, 5, 1), (128, 8, 1), (128, 11, 1)])
+def test_prefill_attention_many_prompts(hd, n_heads, n_kv):
+    """200 prompts at once (work-groups of a kv head's query heads) give the bits of two (a wave per
+    head and 16 positions), whose values the oracle checks above."""
+    shape = synth.Shape("heads", 1, 128, n_heads, n_kv, hd, 128, 300, 1e6, synth.DT_BF16)
+    model = engine.Model(shape, synth.make_weights(shape, 31))
+    for P in (1, 17, 33, 131):
+        prompts = synth.make_prompts(synth.Workload("t", shape, 200, 1, P, 1), P)
+        got = []
+        for n in (200, 2):
+            kv = engine.KVCache(model, 64 if P > 64 else 32, n, P + 1, n * (P // 32 + 2))
+            got.append(engine.prefill(model, kv, dev_i32(prompts[:n]), 1, list(range(n))).cpu().numpy())
+        np.testing.assert_array_equal(got[0][:2].view(np.uint32), got[1].view(np.uint32))
