@@ -307,7 +307,9 @@ int dash_decode_step_grouped(dash_model* model, dash_kv* kv, const int32_t* d_to
  * log softmax(l / T) at the drawn token; d_row_max_lse [n_rows, 2] float32
  * (nullable): per row m = max_v l_v / T and ln sum_v exp(l_v / T), so that
  * log softmax(l / T)_v = l_v / T - that second value for any v (both NaN for a
- * row without a finite logit); d_status (nullable, device uint32): bits OR-ed
+ * row without a finite logit; where a finite logit's quotient overflows float32,
+ * m is +inf and the log-probability and the second value are NaN); d_status
+ * (nullable, device uint32): bits OR-ed
  * in, DASH_ST_NO_FINITE_LOGIT when a row has no finite logit.  DASH_EINVAL if
  * temperature <= 0 or not finite, vocab < 1 or > 2^28, or ld < vocab.
  */

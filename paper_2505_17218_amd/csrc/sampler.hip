@@ -50,19 +50,27 @@ constexpr float kScreenTol = 1.6e-5f;
 
 DASH_DEV bool better(float s, int i, float bs, int bi) { return s > bs || (s == bs && i < bi); }
 
-// Four entries into an online (max mx, sum z of e^(v - mx)): one rescale of the sum to the
-// new maximum, then the four terms, added in pairs.  Non-finite entries are skipped.  The
-// sampler and the log-prob gather share it, so they sum in the same way.  A sum of the
-// four that is finite shows that all four are (an overflowing sum only takes the longer
-// way); waves without a non-finite entry skip the per-entry masks.
-DASH_DEV void lse_push4(float& mx, float& z, const float (&x)[4]) {
+// Four entries x, whose maximum is m4 (where all are finite), into an online (max mx, sum z of
+// e^(v - mx)): one rescale of the sum to the new maximum, then the four terms, added in pairs.
+// Entries whose logit l is not finite are skipped; x differs from l by a temperature unless
+// UNIT_T, and a quotient that overflows counts (+inf leaves no finite sum, -inf adds nothing).
+// The sampler and the log-prob gather share it, so they sum in the same way.  A sum of the
+// four that is finite shows that all four are (an overflowing sum only takes the longer way);
+// waves without a non-finite entry skip the per-entry masks.
+template <bool UNIT_T>
+DASH_DEV void lse_push4(float& mx, float& z, const float (&x)[4], float m4, const float (&l)[4], float temperature = 1.f) {
     float v[4] = {x[0], x[1], x[2], x[3]};
     const float s = (v[0] + v[1]) + (v[2] + v[3]);
     if (__any(!(fabsf(s) < INFINITY))) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = fabsf(v[j]) < INFINITY ? v[j] : -INFINITY;
+        for (int j = 0; j < 4; ++j) {
+            if (fabsf(v[j]) < INFINITY) continue;
+            v[j] = -INFINITY;
+            if (!UNIT_T && fabsf(l[j]) < INFINITY) v[j] = div_rn(l[j], temperature);
+        }
+        m4 = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
     }
-    const float m = fmaxf(mx, fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
+    const float m = fmaxf(mx, m4);
     const float ref = m == -INFINITY ? 0.f : m;  // nothing finite yet: every term is e^-inf = 0
     const float a = __expf(mx - ref);
     const float e0 = __expf(v[0] - ref), e1 = __expf(v[1] - ref), e2 = __expf(v[2] - ref), e3 = __expf(v[3] - ref);
@@ -202,16 +210,21 @@ sample_k(const float* __restrict__ logits, int64_t ld, int vocab, const int32_t*
             if constexpr (UNIT_T) {
                 sc[j] = l[j];
             } else {
-                // l / T by a product and one corrected step (within the margin of the exact
-                // quotient, which the candidates below get; non-finite values stay non-finite)
+                // l / T by a product and one corrected step: within the margin of the exact quotient,
+                // which the candidates below get, or NaN where it overflows
                 const float q = l[j] * inv_t;
                 sc[j] = __builtin_fmaf(__builtin_fmaf(-q, temperature, l[j]), inv_t, q);
             }
         }
         // No entry of the group can reach the bound, even with the group's largest noise:
-        // true for almost every group once the bound has risen.  (The maxima pass over NaN
-        // entries, which can win nothing; infinities fail the comparison.)
-        const float m4 = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
+        // true for almost every group once the bound has risen.  Infinities fail the comparison,
+        // and so does NaN: at a temperature it also stands for finite logits whose quotient (or
+        // 1 / T) overflows, which win, so there the maximum keeps it.  At temperature 1 it
+        // is a NaN logit, which can win nothing, and is passed over.
+        float m4;
+        if constexpr (UNIT_T) m4 = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
+        else m4 = __builtin_elementwise_maximum(__builtin_elementwise_maximum(sc[0], sc[1]),
+                                                __builtin_elementwise_maximum(sc[2], sc[3]));
         const float hi4 = m4 + noise_bound(max(max(x.x, x.y), max(x.z, x.w)));
         if (__any(!(hi4 + screen_margin(hi4) < floor_w))) {
             const uint32_t xs[4] = {x.x, x.y, x.z, x.w};
@@ -239,7 +252,7 @@ sample_k(const float* __restrict__ logits, int64_t ld, int vocab, const int32_t*
             if (f > floor_w && (threadIdx.x & 63) == 0)
                 (void)__hip_atomic_fetch_max(&floor_s, f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        lse_push4(mx, z, sc);
+        lse_push4<UNIT_T>(mx, z, sc, m4, l, temperature);
     };
     // Two groups in flight per lane, in two register sets that take turns: a set is
     // copied out right after the other set's load has been issued (so the wait before the
@@ -378,7 +391,7 @@ logprob_gather_k(const float* __restrict__ logits, int64_t ld, int vocab, const 
     const __amdgpu_buffer_rsrc_t rs = row_rsrc(row, vocab);
     auto push = [&](float (&l)[4], int g0) {
         if (4 * (g0 + 64) > vocab) vocab_mask(l, g0 + (threadIdx.x & 63), vocab);  // wave-uniform
-        lse_push4(mx, z, l);
+        lse_push4<true>(mx, z, l, fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3])), l);
     };
     if (lane0 < n4) {  // sample_k's loads: two groups in flight in sets that take turns
         float set_a[4], set_b[4], l[4];
@@ -566,7 +579,7 @@ kl_rows_k(const float* __restrict__ theta, const float* __restrict__ base, int64
                 }
             }
             kl_push4(sa, sb, a, b);
-            if constexpr (LP) lse_push4(mx[v], z[v], a);
+            if constexpr (LP) lse_push4<true>(mx[v], z[v], a, fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])), a);
         }
     }
     const int w = threadIdx.x >> 6;

@@ -141,6 +141,40 @@ def test_sample_masked_rows_and_group_edges(V, temp):
     np.testing.assert_allclose(lps.cpu().numpy(), want_lp, atol=LP_ATOL + 2.0 ** -22 * 15.0 / temp, rtol=LP_RTOL)
 
 
+@pytest.mark.parametrize("V", [5000, 8195])
+@pytest.mark.parametrize("temp,big,rest,small", [
+    (1e-36, 400.0, 2.0, 1.0),   # the quotient of one logit overflows
+    (0.7, 3e38, 20.0, 1.0),     # a token forced by a huge finite logit
+    (2e-39, 2.0, 0.3, 0.1),     # the reciprocal of the temperature overflows too
+    (2e-39, 0.5, 0.3, 0.1)])    # ... and no quotient does
+def test_sample_overflowing_quotients(V, temp, big, rest, small):
+    """A finite logit whose quotient l / T overflows scores +inf and is drawn, past the workgroup's
+    first pass as well, where the neighbours of its group are far below the bound; of several
+    the smallest index.  A quotient of -inf adds nothing to the normaliser."""
+    at = [[4501], [7], [V - 1], [4096], [4097, 4501, V - 1]]
+    logits = np.full((len(at), V), small, np.float32)
+    logits[:, 10:4000:97] = rest
+    logits[:, 1:V - 1:101] = -3.0 if temp < 1e-37 else -20.0
+    for row, cols in zip(logits, at):
+        row[cols] = big
+    uid, step = np.arange(len(at), dtype=np.int32), np.full(len(at), 5, np.int32)
+    ml = torch.empty(len(at), 2, device="cuda")
+    toks, lps = engine.sample(torch.from_numpy(logits).cuda(), dev_i32(uid), dev_i32(step), temp, 12, row_max_lse=ml)
+    with np.errstate(over="ignore"):
+        want_t, _ = osm.sample(logits, uid, step, temp, 12)
+        top = np.float32(big) / np.float32(temp)
+    np.testing.assert_array_equal(toks.cpu().numpy(), want_t)
+    ml = ml.cpu().numpy()
+    if np.isinf(top):  # a score that float32 cannot hold has no log-probability
+        assert np.isinf(ml[:, 0]).all() and np.isnan(ml[:, 1]).all() and np.isnan(lps.cpu().numpy()).all()
+    else:
+        assert (ml == top).all()
+        # the drawn tokens hold the largest logit; every other term is e^-(0.2 / T) = 0.  (From scores of
+        # 2.5e38 even float64 does not resolve the logarithm of their number.)
+        want_lp = [-np.log(len(cols)) for cols in at]
+        np.testing.assert_allclose(lps.cpu().numpy(), want_lp, atol=LP_ATOL)
+
+
 def test_sample_deterministic_and_independent_of_batch_position():
     logits = synth.make_logits(8, 151936, seed=5)
     uid = np.arange(8, dtype=np.int32)
