@@ -264,19 +264,20 @@ struct LossArgs {
     double *loss, *seq_lp, *stats;
 };
 
-// Sum of row[0 .. L-1] over the wave, the same value in every lane.
+// Sum of row[0 .. L-1] over the wave, the same value in every lane.  (t runs up to 575 past L:
+// unsigned, so that it doesn't wrap at the largest L.)
 DASH_DEV double loss_row_sum(const float* __restrict__ row, int L) {
-    const int lane = threadIdx.x & 63;
+    const uint32_t n = (uint32_t)L;
     double acc = 0.0;
-    int t = lane;
-    for (; t + 7 * 64 < L; t += 8 * 64) {  // eight loads in flight per lane
+    uint32_t t = threadIdx.x & 63;
+    for (; t + 7 * 64 < n; t += 8 * 64) {  // eight loads in flight per lane
         float v[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) v[j] = row[t + 64 * j];
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc += (double)v[j];
     }
-    for (; t < L; t += 64) acc += (double)row[t];
+    for (; t < n; t += 64) acc += (double)row[t];
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) acc += __shfl_xor(acc, o, 64);
     return acc;

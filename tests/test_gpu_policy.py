@@ -280,3 +280,14 @@ def test_loss_routes_bit_identical(N, T):
     assert abs(got[0] - want) <= 1e-12 * max(1.0, abs(want))
     assert got[0] == got[1] and got[2] == got[3]
     np.testing.assert_array_equal(seq.cpu().numpy(), stats.cpu().numpy()[:, 0])
+
+
+def test_loss_row_of_the_largest_length():
+    """A row of 2^31 - 1 tokens, the most that the length's type holds: the lanes' strides of 64 and
+    512 tokens step past its end without wrapping."""
+    T = 2 ** 31 - 1
+    lp = torch.zeros(1, T, device="cuda")
+    lp[0, ::2 ** 28] = -1.0
+    lp[0, T - 1] = -0.5
+    loss, seq = engine.pg_loss(lp, torch.tensor([2.0], device="cuda"), dev_i32([0]))
+    assert float(seq.item()) == -8.5 and float(loss.item()) == 17.0
