@@ -53,6 +53,15 @@ DASH_DEV int xcd_remap(int bid, int nb) {
     return x * q + (x < r ? x : r) + j;
 }
 
+// Between a wave's LDS writes and its reads of what other lanes wrote (or the other way round)
+// where the LDS is the wave's own: a wave's LDS operations complete in order, so nothing is
+// waited for, but the compiler sees one lane's accesses, of different types and addresses, and
+// may otherwise reorder them.
+DASH_DEV void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Rotate-half RoPE of the pair (a, b) = (z_i, z_{i + hd/2}) by the angle with
 // cosine c and sine s: lo = a c - b s, hi = b c + a s.  Written as one fused
 // multiply-add over a separately rounded product, so every kernel that rotates

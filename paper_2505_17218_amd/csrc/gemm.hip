@@ -704,6 +704,7 @@ DASH_DEV void wide_qkv_epilogue(const f32x16_t (&acc)[TM][4], const QkvRopeArgs&
                     hp[rr * kQkvRow + half] = f2bf(hi);
                 }
             }
+            wave_lds_fence();
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int rr = u * 4 + (lane >> 4), c8 = (lane & 15) * 8, m = m0 + b0 + rr;
@@ -717,6 +718,7 @@ DASH_DEV void wide_qkv_epilogue(const f32x16_t (&acc)[TM][4], const QkvRopeArgs&
                     *reinterpret_cast<uint4*>(kb + k_index_bf16(g, rows.key[b0 + rr], jj & (hd - 1))) = v;
                 }
             }
+            wave_lds_fence();
         }
         return;
     }
@@ -966,6 +968,7 @@ gemm_wide_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __
                     for (int r = 0; r < 16; ++r)
                         Hs[(i * 32 + (r >> 2) * 8 + fhalf * 4 + (r & 3)) * OS + j * 32 + frow] =
                             f2bf(silu(acc[i][j][r]) * acc[i][j + TN / 2][r]);
+            wave_lds_fence();
 #pragma unroll
             for (int u = 0; u < WM * OW / 8 / 64; ++u) {
                 const int run = lane + u * 64, rr = run / (OW / 8), c8 = run % (OW / 8) * 8;
@@ -1130,9 +1133,11 @@ gemm_wide_persist_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, 
                         *reinterpret_cast<f32_lds_t*>(mine + w0 + at) = acc[i][0][hh * 8 + r];
                         *reinterpret_cast<f32_lds_t*>(mine + w1 + at) = acc[i][1][hh * 8 + r];
                     }
+                    wave_lds_fence();
 #pragma unroll
                     for (int u = 0; u < 4; ++u)
                         put(*reinterpret_cast<const u32x4_t*>(mine + (u & 1 ? r1 : r0) + u * 1024), i * 32 + hh * 16 + u * 4);
+                    wave_lds_fence();
                     __builtin_amdgcn_sched_barrier(0);  // one chunk's registers at a time
                 }
         } else {
@@ -1145,9 +1150,11 @@ gemm_wide_persist_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, 
                 for (int r = 0; r < 16; ++r)
                     *reinterpret_cast<bf16_lds_t*>(mine + w0 + ((r >> 2) * 8 + (r & 3)) * (OS * 2)) =
                         f2bf(silu(acc[i][0][r]) * acc[i][1][r]);
+                wave_lds_fence();
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
                     put(*reinterpret_cast<const u32x4_t*>(mine + r0 + u * 16 * (OS * 2)), i * 32 + u * 16);
+                wave_lds_fence();
                 __builtin_amdgcn_sched_barrier(0);  // one chunk's registers at a time
             }
         }
