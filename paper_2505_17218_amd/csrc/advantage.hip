@@ -251,7 +251,8 @@ live_compact_k(const int32_t* __restrict__ tok, const int32_t* __restrict__ slot
 // sums in the caller's stats (or seq_lp) for the one-workgroup sum.  One thread per sample
 // in a single workgroup took 560 us at 1024 x 1024 (three rows, 614 kept, mean length
 // 512): uncoalesced 4-byte reads and a serial chain of adds on one CU; the two launches
-// take under 10 us (the call 593 -> 24 us, most of it the host).  Without either output the one workgroup's waves read the rows too.
+// take under 10 us (the call 593 -> 24 us, most of it the host).  Without an output that holds
+// the sums the one workgroup's waves read the rows too.
 struct LossArgs {
     const float *lp, *lp_old, *kl;
     int64_t ld;
@@ -397,9 +398,10 @@ hipError_t launch_policy_loss(const float* lp, const float* lp_old, const float*
                               int n_total, double clip_eps, double beta, double* loss, double* seq_lp, double* stats,
                               hipStream_t st) {
     const LossArgs a{lp, lp_old, kl, ld, T, len, adv, kept, kept_count, n_total, clip_eps, beta, loss, seq_lp, stats};
+    if (seq_lp && !stats && (lp_old || kl)) return hipErrorInvalidValue;
     // the sums' way from the row launch to the final one: stats, or seq_lp where S is all there is
-    const int from = stats ? 1 : seq_lp && !lp_old && !kl ? 2 : 0;
-    if (from || seq_lp) {
+    const int from = stats ? 1 : seq_lp ? 2 : 0;
+    if (from) {
         const int blocks = n_total / kLossRowWaves < 2048 ? n_total / kLossRowWaves + 1 : 2048;
         loss_rows_k<<<blocks, 64 * kLossRowWaves, 0, st>>>(a);
     }

@@ -1271,7 +1271,7 @@ hipError_t run_wide_cols(const void* A, const void* W, void* C, int M, int N, in
             return run(std::false_type{});
         }
     }
-    if constexpr (EPI == EPI_STORE_F32)
+    if constexpr (EPI == EPI_STORE_F32 && BM == 256 && BN == 256)  // the others run where one round holds the launch
         if (past_cache) {
             gemm_wide_k<WGM, WGN, TM, TN, EPI, S, true><<<blocks, 64 * WGM * WGN, 0, st>>>(
                 (const bf16_t*)A, (const bf16_t*)W, C, M, N, K, ldc, m_tiles, n_tiles, col0 / tn, gm, kps, split_stride, qa);
@@ -1500,7 +1500,8 @@ gemm_stream_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* 
     wait_vmcnt<0>();  // the out-of-range loads of the steps past the end still write their stages
 }
 
-template <int WM_, int WN_, int TN, int U, int S, int EPI>
+// ONE_ROW: a tile for batches of at most its rows
+template <int WM_, int WN_, int TN, int U, int S, int EPI, bool ONE_ROW = false>
 hipError_t run_stream(const void* A, const void* W, void* C, int M, int N, int K, int ldc, int nsplit,
                       size_t split_stride, hipStream_t st) {
     constexpr int BM = 32 * WM_, BN = U * TN * WN_;
@@ -1511,9 +1512,12 @@ hipError_t run_stream(const void* A, const void* W, void* C, int M, int N, int K
     if (K % kBK || (size_t)M * K * 2 >= (1u << 31) || (size_t)N * K * 2 >= (1u << 31)) return hipErrorInvalidValue;
     const int blocks = m_tiles * n_tiles * nsplit;
     // a weight byte that one work-group alone reads streams past the caches
-    if (m_tiles == 1)
+    if (m_tiles == 1) {
         gemm_stream_k<WM_, WN_, TN, U, S, EPI, 2><<<blocks, 64 * WM_ * WN_, 0, st>>>(
             (const bf16_t*)A, (const bf16_t*)W, C, M, N, K, ldc, m_tiles, n_tiles, kps, split_stride);
+        return hipGetLastError();
+    }
+    if constexpr (ONE_ROW) return hipErrorInvalidValue;
     else
         gemm_stream_k<WM_, WN_, TN, U, S, EPI, 0><<<blocks, 64 * WM_ * WN_, 0, st>>>(
             (const bf16_t*)A, (const bf16_t*)W, C, M, N, K, ldc, m_tiles, n_tiles, kps, split_stride);
@@ -1774,16 +1778,16 @@ hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C
             // 24.7, 32.5).  129-256 rows with more tiles than CUs stay register-staged (1.5B
             // 25.4 against 27-35 us at 192 rows).
             const long t64 = (N / 2 + 63) / 64;
-            if (M <= 32) return run_stream<1, 1, 2, 16, 4, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
-            if (M <= 64 && t64 < 128) return run_stream<2, 1, 2, 32, 4, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
+            if (M <= 32) return run_stream<1, 1, 2, 16, 4, EPI_SWIGLU, true>(A, W, C, M, N, K, ldc, 1, 0, st);
+            if (M <= 64 && t64 < 128) return run_stream<2, 1, 2, 32, 4, EPI_SWIGLU, true>(A, W, C, M, N, K, ldc, 1, 0, st);
             if ((M + 63) / 64 * t64 <= 256) return run_stream<2, 2, 2, 32, 4, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
             if ((M + 127) / 128 * t64 <= 256) return run_stream<4, 2, 2, 32, 4, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
             return run_bf16<64, 128, 2, 2, 2, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, st);
         }
         if (N >= 8192) {  // LM head: many tiles, the largest tile that the batch fills wins
             // one row block: two work-groups of four 32 x 32 (eight) blocks a CU
-            if (M <= 32) return run_stream<1, 4, 1, 32, 4, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
-            if (M <= 64) return run_stream<2, 4, 1, 32, 3, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
+            if (M <= 32) return run_stream<1, 4, 1, 32, 4, EPI_STORE_F32, true>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
+            if (M <= 64) return run_stream<2, 4, 1, 32, 3, EPI_STORE_F32, true>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             if (M <= 128)  // measured 10-18% faster than 256x256 at 96-128 rows
                 return run_bf16<128, 256, 4, 4, 2, EPI_STORE_F32>(A, W, C, M, N, K, ldc, nsplit, split_stride, st);
             // wide tiles past one 256-row block (there 2% slower at K = 2048): 0.5B at 419 rows 169
