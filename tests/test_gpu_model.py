@@ -153,9 +153,9 @@ BF16_D = synth.Shape("bf16-ff4096", 1, 256, 4, 2, 64, 4096, 500, 1e6, synth.DT_B
 
 @pytest.mark.parametrize("n_prompts", [10, 75, 150])
 def test_bf16_gemm_tile_regimes(n_prompts):
-    """Decode batches of 40, 300 and 600 rows select different GEMM tiles (narrow
-    small-batch tiles, 64x64, 128x256 for the split-K down projection); all match the
-    oracle, and a row's logits do not depend on the regime its batch falls in."""
+    """Decode batches of 40, 300 and 600 rows select different GEMM tiles (for the split-K down
+    projection streaming ones of 32x32, 64x64 and 128x64); all match the oracle, and a row's
+    logits do not depend on the regime its batch falls in."""
     shape = BF16_D
     w = synth.make_weights(shape, 8)
     wl = synth.Workload("t", shape, 150, 4, 12, 3)
@@ -172,14 +172,14 @@ def test_bf16_gemm_tile_regimes(n_prompts):
         np.testing.assert_array_equal(small.logits[0], run.logits[0][:40])
 
 
-# d_ff = 2240 (18 columns of 128-wide SwiGLU tile pairs): a 1024-row decode batch runs
-# gate/up on 128x256 tiles (144, under one round), a 40-row batch on 64x64 tiles
+# d_ff = 2240 (35 columns of 64-wide SwiGLU tile pairs): a 1024-row decode batch runs gate/up on
+# 256x128 tiles (140, under one round), a 40-row batch on streaming tiles of 32 columns of h
 BF16_E = synth.Shape("bf16-ff2240", 1, 256, 4, 2, 64, 2240, 500, 1e6, synth.DT_BF16)
 
 
 def test_bf16_swiglu_tile_regimes_bitexact():
-    """1024 decode rows (128x256 SwiGLU tiles) give every row the same logits, bit for bit,
-    as a 40-row batch (64x64 tiles), and match the oracle."""
+    """1024 decode rows (256x128 SwiGLU tiles) give every row the same logits, bit for bit,
+    as a 40-row batch (streaming tiles), and match the oracle."""
     shape = BF16_E
     w = synth.make_weights(shape, 9)
     wl = synth.Workload("t", shape, 256, 4, 10, 2)
@@ -196,7 +196,7 @@ def test_bf16_swiglu_tile_regimes_bitexact():
 
 # d_ff = 8320 (65 columns of 128-wide SwiGLU tile pairs): at 1024 rows one round of 256x256
 # tiles covers 8192 columns (260 tiles would leave a last round of 4), so gate/up runs as two
-# launches, 256x256 over those columns and 64x128 over the last 128; 40 rows on 64x64 tiles
+# launches, 256x256 over those columns and 64x128 over the last 128; 40 rows on streaming tiles
 BF16_I = synth.Shape("bf16-ff8320", 1, 256, 4, 2, 64, 8320, 500, 1e6, synth.DT_BF16)
 
 
@@ -218,20 +218,19 @@ def test_bf16_swiglu_tile_rounds_bitexact():
         assert np.abs(ref - big.logits[:, n, :]).max() <= TOL[shape.dtype], n
 
 
-# d_ff = 8192 (128 SwiGLU tiles of 64 column pairs): gate/up runs on 64x128 tiles with three
-# k-steps in flight up to 64 rows, on 64x64 tiles at 65-128 rows, on 64x128 tiles with two
-# k-steps in flight at 129-256 rows, on 128x128 tiles at 300 rows, on 256x256 tiles at 480
-# and 1024 rows (one round of 128 / 256 of them) and on 128x128 tiles again at 2048 rows
-# (512 = two exact rounds of 256x256, 1024 = four of 128x256); the down projection
-# (K = 8192, split) on 64x32 tiles four k-steps ahead, 64x64 tiles three or two k-steps
-# ahead, direct-to-LDS 128x128 tiles (480 rows), 128x256 or 256x256; the output projection
-# on 64x32 tiles, 64x64 tiles three or two k-steps ahead, direct-to-LDS or 256x256 tiles
+# d_ff = 8192: gate/up runs on streaming tiles of 32 rows x 16 columns of h at 20 rows, 64 x 64 up
+# to 128 and 128 x 64 up to 256 rows, on 128x128 tiles at 300 rows, on 256x256 tiles at 480 and
+# 1024 rows (one round of 128 / 256 of them), on 128x128 direct-to-LDS tiles at 2048 rows (512 =
+# two exact rounds of 256x256), in two launches by columns at 1200 and in work-groups that
+# stay at 2560 and 5120; the down projection (K = 8192, split) on streaming tiles from 32x32 to
+# 128x64, 256x128 and 256x256; the output projection on streaming tiles from 32x16 to 64x32,
+# direct-to-LDS 64x64 and 256x256 tiles
 BF16_G = synth.Shape("bf16-ff8192", 1, 256, 4, 2, 64, 8192, 500, 1e6, synth.DT_BF16)
 
 
 def test_bf16_gemm_regimes_across_batch_sizes_bitexact():
-    """Batches of 10 to 512 prompts (prefill 100 to 5120 rows, decode 40 to 2048 rows) run
-    every gate/up, down and output projection tiling; the rows they share get the same
+    """Batches of 5 to 512 prompts (prefill 50 to 5120 rows, decode 20 to 2048 rows) run the
+    gate/up, down and output projections on the tiles above; the rows they share get the same
     logits bit for bit, and sampled rows match the oracle."""
     shape = BF16_G
     w = synth.make_weights(shape, 11)
@@ -239,12 +238,14 @@ def test_bf16_gemm_regimes_across_batch_sizes_bitexact():
     prompts = synth.make_prompts(wl, 11)
     model = engine.Model(shape, w)
     runs = {n: run_stepwise(model, make_kv(model, 32, 4 * n, 12), prompts[:n], 4, 2, 1.0, 5)
-            for n in (10, 25, 50, 75, 120, 256, 512)}
+            for n in (5, 10, 25, 50, 75, 120, 256, 512)}
     for n in (25, 50, 75, 120, 256, 512):
         np.testing.assert_array_equal(runs[10].logits[0], runs[n].logits[0][:40])  # prefill
         np.testing.assert_array_equal(runs[10].logits[1], runs[n].logits[1][:40])  # decode step
+    np.testing.assert_array_equal(runs[5].logits[0], runs[10].logits[0][:20])
+    np.testing.assert_array_equal(runs[5].logits[1], runs[10].logits[1][:20])
     sd = shape_dict(shape)
-    for n_prompts, n in ((10, 0), (25, 99), (50, 199), (75, 299), (120, 479), (256, 1023), (512, 2047)):
+    for n_prompts, n in ((5, 19), (10, 0), (25, 99), (50, 199), (75, 299), (120, 479), (256, 1023), (512, 2047)):
         run = runs[n_prompts]
         ref = om.rollout_logits(sd, w, prompts[n // 4], run.tokens[n])
         assert np.abs(ref - run.logits[:, n, :]).max() <= TOL[shape.dtype], (n_prompts, n)
@@ -258,7 +259,7 @@ def test_bf16_swiglu_column_split_bitexact(ff, n_prompts, rest):
     rounds of 256x256 tiles would leave a last round under half full: the columns of the
     whole rounds run as one launch and the rest (on the tile named by `rest`) as another
     (1100 rows, 275 prompts: partial row tiles in both launches, columns split at 6528).
-    The rows shared with a 40-row batch (64x64 tiles) get the same logits bit for bit, and
+    The rows shared with a 40-row batch (streaming tiles) get the same logits bit for bit, and
     sampled rows match the oracle."""
     shape = synth.Shape(f"bf16-ff{ff}", 1, 256, 4, 2, 64, ff, 500, 1e6, synth.DT_BF16)
     w = synth.make_weights(shape, 13)
@@ -275,25 +276,26 @@ def test_bf16_swiglu_column_split_bitexact(ff, n_prompts, rest):
         assert np.abs(ref - big.logits[:, n, :]).max() <= TOL[shape.dtype], n
 
 
-# vocab 9000 (>= 8192 columns: the LM head's tiles): 64x256 up to 64 rows, 128x256 up to 128,
-# 256x256 past that
+# vocab 9000 (>= 8192 columns: the LM head's tiles): streaming 32x128 up to 32 rows and 64x128 up to
+# 64, register-staged 128x256 up to 128 and 256x256 up to 256, direct-to-LDS 256x256 past that
 BF16_H = synth.Shape("bf16-v9000", 1, 256, 4, 2, 64, 512, 9000, 1e6, synth.DT_BF16)
 
 
 def test_bf16_lm_head_regimes_bitexact():
-    """Batches of 10, 25 and 75 prompts put the LM head on 64x256, 128x256 and 256x256 tiles
-    (prefill 10 / 25 / 75 rows, decode 40 / 100 / 300 rows); the rows they share get the same
-    logits bit for bit, and sampled rows match the oracle."""
+    """Batches of 10, 25, 50 and 75 prompts put the LM head on each of those tiles (prefill 10 / 25 /
+    50 / 75 rows, decode 40 / 100 / 200 / 300 rows); the rows they share get the same logits bit
+    for bit, and sampled rows match the oracle."""
     shape = BF16_H
     w = synth.make_weights(shape, 14)
     prompts = synth.make_prompts(synth.Workload("t", shape, 75, 4, 10, 2), 14)
     model = engine.Model(shape, w)
-    runs = {n: run_stepwise(model, make_kv(model, 32, 4 * n, 12), prompts[:n], 4, 2, 1.0, 5) for n in (10, 25, 75)}
-    for n in (25, 75):
+    runs = {n: run_stepwise(model, make_kv(model, 32, 4 * n, 12), prompts[:n], 4, 2, 1.0, 5)
+            for n in (10, 25, 50, 75)}
+    for n in (25, 50, 75):
         np.testing.assert_array_equal(runs[10].logits[0], runs[n].logits[0][:40])  # prefill
         np.testing.assert_array_equal(runs[10].logits[1], runs[n].logits[1][:40])  # decode step
     sd = shape_dict(shape)
-    for n_prompts, n in ((10, 0), (25, 99), (75, 299)):
+    for n_prompts, n in ((10, 0), (25, 99), (50, 199), (75, 299)):
         run = runs[n_prompts]
         ref = om.rollout_logits(sd, w, prompts[n // 4], run.tokens[n])
         assert np.abs(ref - run.logits[:, n, :]).max() <= TOL[shape.dtype], (n_prompts, n)
@@ -658,9 +660,9 @@ def test_stale_nonfinite_pool_bytes_do_not_change_results(shape, P, T):
 @pytest.mark.parametrize("hd,n_heads,n_kv", [(64, 2, 2), (64, 4, 2), (64, 6, 2), (64, 7, 1), (64, 9, 1), (64, 16, 1),
                                              (128, 1, 1), (128, 2, 1), (128, 3, 1), (128, 5, 1), (128, 8, 1), (128, 11, 1)])
 def test_prefill_attention_head_groups(hd, n_heads, n_kv):
-    """Prefill attention over every size of head group (waves per work-group, heads in two
-    halves, several position blocks per work-group), at lengths around the 16-position and
-    32-key blocks and past three blocks, against the oracle."""
+    """Prefill attention of two prompts (a wave per head and 16 positions) over every size of head
+    group, at lengths around the 16-position and 32-key blocks and past three blocks, against
+    the oracle."""
     shape = synth.Shape("heads", 1, 128, n_heads, n_kv, hd, 128, 300, 1e6, synth.DT_BF16)
     w = synth.make_weights(shape, 31)
     model = engine.Model(shape, w)
@@ -677,14 +679,17 @@ def test_prefill_attention_head_groups(hd, n_heads, n_kv):
 @pytest.mark.parametrize("hd,n_heads,n_kv", [(64, 2, 2), (64, 4, 2), (64, 6, 2), (64, 7, 1), (64, 9, 1), (64, 16, 1),
                                              (128, 1, 1), (128, 2, 1), (128, 3, 1), (128, 5, 1), (128, 8, 1), (128, 11, 1)])
 def test_prefill_attention_many_prompts(hd, n_heads, n_kv):
-    """200 prompts at once (work-groups of a kv head's query heads) give the bits of two (a wave per
-    head and 16 positions), whose values the oracle checks above."""
+    """200 prompts at once (work-groups of a kv head's query heads: every count of waves per
+    work-group, heads in two halves, several position blocks) give the bits of two at a time (a
+    wave per head and 16 positions, whose values the oracle checks above), the first, those in
+    the middle and the last of them."""
     shape = synth.Shape("heads", 1, 128, n_heads, n_kv, hd, 128, 300, 1e6, synth.DT_BF16)
     model = engine.Model(shape, synth.make_weights(shape, 31))
     for P in (1, 17, 33, 131):
         prompts = synth.make_prompts(synth.Workload("t", shape, 200, 1, P, 1), P)
-        got = []
-        for n in (200, 2):
+        got = {}
+        for at, n in ((0, 200), (0, 2), (99, 2), (198, 2)):
             kv = engine.KVCache(model, 64 if P > 64 else 32, n, P + 1, n * (P // 32 + 2))
-            got.append(engine.prefill(model, kv, dev_i32(prompts[:n]), 1, list(range(n))).cpu().numpy())
-        np.testing.assert_array_equal(got[0][:2].view(np.uint32), got[1].view(np.uint32))
+            got[at, n] = engine.prefill(model, kv, dev_i32(prompts[at:at + n]), 1, list(range(n))).cpu().numpy()
+        for at in (0, 99, 198):
+            np.testing.assert_array_equal(got[0, 200][at:at + 2].view(np.uint32), got[at, 2].view(np.uint32))

@@ -114,13 +114,27 @@ WIDE_E = synth.Shape("wide-persistent-k64", 1, 64, 6, 1, 64, 1024, 300, 1e6, syn
 # five splits: at 5440 rows left as partials by the work-groups that stay, at 6375 summed on 128x256 tiles
 WIDE_F = synth.Shape("wide-five-splits", 1, 1536, 4, 2, 64, 4160, 300, 1e6, synth.DT_BF16)
 WIDE_C = synth.Shape("wide-k64", 1, 64, 6, 1, 64, 64, 300, 1e6, synth.DT_BF16)
+# the output projection's four-stage 128x128 tiles (1536 columns at 1665 rows), with one, two and three steps past
+# the last four of its loop
+WIDE_G = [synth.Shape(f"wide-o{h}", 1, 1536, h, 1, 64, 64, 300, 1e6, synth.DT_BF16) for h in (5, 6, 7)]
+WIDE_H = synth.Shape("wide-o2048", 1, 2048, 6, 2, 64, 64, 300, 1e6, synth.DT_BF16)  # its 128x128 tiles of the LDS ring
+WIDE_K = synth.Shape("o4096", 1, 4096, 4, 1, 64, 64, 300, 1e6, synth.DT_BF16)  # 150 rows: 64x32 register-staged tiles
+# split QKV and output projections (5120 x 4096, 4096 x 4096): streaming tiles of 64x64 at 60 and 128x64 at 100 rows
+WIDE_L = synth.Shape("qkv5120", 1, 4096, 64, 8, 64, 64, 300, 1e6, synth.DT_BF16)
+# 16-byte runs impossible: an LM head of 304 MB (streaming stores) from work-groups of one tile
+WIDE_J = synth.Shape("wide-v33001", 1, 320, 4, 2, 64, 448, 33001, 1e6, synth.DT_BF16)
 
 
 @pytest.mark.parametrize("shape,n,P,L_", [(WIDE_A, 8, 600, 701),    # 128x128 QKV tiles, rows off the pages
                                           (WIDE_A, 16, 650, 704),   # 256x256 QKV tiles, whole pages of keys
                                           (WIDE_B, 5, 640, 701), (WIDE_B, 10, 660, 701),
                                           (WIDE_C, 65, 500, 512), (WIDE_D, 16, 636, 704), (WIDE_D, 15, 632, 701),
-                                          (WIDE_E, 65, 500, 512), (WIDE_F, 8, 650, 680), (WIDE_F, 15, 400, 425)])
+                                          (WIDE_E, 65, 500, 512), (WIDE_F, 8, 650, 680), (WIDE_F, 15, 400, 425),
+                                          (WIDE_F, 4, 50, 75),      # down: 64x64 register-staged tiles
+                                          *((g, 5, 300, 333) for g in WIDE_G), (WIDE_H, 5, 300, 333),
+                                          (WIDE_F, 4, 10, 15),      # down: 64x32 streaming tiles, one row block
+                                          (WIDE_K, 2, 50, 75), (WIDE_L, 4, 10, 15), (WIDE_L, 4, 20, 25),
+                                          (WIDE_D, 16, 560, 704), (WIDE_J, 16, 560, 704)])  # streaming stores
 def test_wide_tiles_bit_identical_to_small_batches(shape, n, P, L_):
     """Many sequences in one forward pass (the wide GEMM tiles, their last row and column tiles
     partly empty, the QKV projection's RoPE and KV append from the accumulators) give the bits of
