@@ -50,6 +50,14 @@ constexpr float kScreenTol = 1.6e-5f;
 
 DASH_DEV bool better(float s, int i, float bs, int bi) { return s > bs || (s == bs && i < bi); }
 
+// Whether any of the wave's logits is finite.  With most of a vocabulary masked to -inf most waves'
+// groups hold none; the log-normaliser and, at a temperature, the scoring then skip them (151,936
+// entries with one in a thousand left, 1024 rows: 133 -> 117 us at T = 1, 145 -> 119 at 0.7).
+// Asked only where a non-finite entry was met.
+DASH_DEV bool wave_any_finite(const float (&l)[4]) {
+    return __any(fminf(fminf(fabsf(l[0]), fabsf(l[1])), fminf(fabsf(l[2]), fabsf(l[3]))) < INFINITY);
+}
+
 // Four entries x, whose maximum is m4 (where all are finite), into an online (max mx, sum z of
 // e^(v - mx)): one rescale of the sum to the new maximum, then the four terms, added in pairs.
 // Entries whose logit l is not finite are skipped; x differs from l by a temperature unless
@@ -62,6 +70,7 @@ DASH_DEV void lse_push4(float& mx, float& z, const float (&x)[4], float m4, cons
     float v[4] = {x[0], x[1], x[2], x[3]};
     const float s = (v[0] + v[1]) + (v[2] + v[3]);
     if (__any(!(fabsf(s) < INFINITY))) {
+        if (!wave_any_finite(l)) return;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if (fabsf(v[j]) < INFINITY) continue;
@@ -226,7 +235,10 @@ sample_k(const float* __restrict__ logits, int64_t ld, int vocab, const int32_t*
         else m4 = __builtin_elementwise_maximum(__builtin_elementwise_maximum(sc[0], sc[1]),
                                                 __builtin_elementwise_maximum(sc[2], sc[3]));
         const float hi4 = m4 + noise_bound(max(max(x.x, x.y), max(x.z, x.w)));
-        if (__any(!(hi4 + screen_margin(hi4) < floor_w))) {
+        bool look = __any(!(hi4 + screen_margin(hi4) < floor_w));
+        // (at temperature 1 this test costs more, 3% where half the vocabulary is masked, than it saves)
+        if (!UNIT_T && look && __all(!(fabsf(m4) < INFINITY))) look = wave_any_finite(l);
+        if (look) {
             const uint32_t xs[4] = {x.x, x.y, x.z, x.w};
             float floor_t = floor_w;
 #pragma unroll

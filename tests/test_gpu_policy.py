@@ -245,6 +245,26 @@ def test_logits_kl_group_edges(V, pad):
     assert np.isnan(kl[4:]).all() and np.isnan(kl_rev[4:]).all()
 
 
+@pytest.mark.parametrize("V", [5000, 5125])
+def test_logits_kl_whole_waves_masked(V):
+    """Entries from 300 to V - 5 masked on both sides (whole waves of -inf pairs), then one with mass
+    on one side only, a NaN on one side, or an infinity."""
+    theta, base = synth.make_logits(4, V, seed=37, scale=4.0), synth.make_logits(4, V, seed=38, scale=4.0)
+    theta[:, 300:V - 5] = base[:, 300:V - 5] = -np.inf
+    theta[1, 3000] = 0.5
+    theta[2, 3000], base[2, 3000] = 0.5, np.nan  # (beside a masked entry the infinity of one-sided mass comes first)
+    theta[3, 3000], base[3, 3000] = np.inf, 0.5
+    kl, kl_rev = (x.cpu().numpy() for x in engine.logits_kl(torch.from_numpy(theta).cuda(), torch.from_numpy(base).cuda()))
+    ref = opol.kl_rows(theta[:2].astype(np.float64), base[:2].astype(np.float64))
+    for r in range(2):
+        for got, want in ((kl[r], ref[0][r]), (kl_rev[r], ref[1][r])):
+            if np.isinf(want):
+                assert got == want
+            else:
+                assert abs(got - want) <= _kl_row_tol(theta[r], base[r], want), (r, got, want)
+    assert np.isnan(kl[2:]).all() and np.isnan(kl_rev[2:]).all()
+
+
 @pytest.mark.parametrize("vocab", [4104, 5122])
 def test_teacher_forced_kl_logprobs_past_one_pass(vocab):
     """The log-probs from the row-KL kernel's pass, over more groups than one unrolled step of its

@@ -141,6 +141,24 @@ def test_sample_masked_rows_and_group_edges(V, temp):
     np.testing.assert_allclose(lps.cpu().numpy(), want_lp, atol=LP_ATOL + 2.0 ** -22 * 15.0 / temp, rtol=LP_RTOL)
 
 
+@pytest.mark.parametrize("temp", [1.0, 0.7])
+@pytest.mark.parametrize("V", [1021, 9000])
+def test_sample_few_unmasked_entries(V, temp):
+    """All but one to eight entries masked to -inf (whole waves without a finite logit, ahead of and
+    behind those that hold one), and a row with NaN and +inf among the masked."""
+    R = 9
+    rng = np.random.default_rng(V)
+    logits = np.full((R, V), -np.inf, np.float32)
+    for r in range(R - 1):
+        logits[r, rng.choice(V, r + 1, replace=False)] = rng.standard_normal(r + 1) * 3
+    logits[R - 1, ::3], logits[R - 1, 1::3], logits[R - 1, V // 2] = np.nan, np.inf, 1.5
+    uid, step = np.arange(R, dtype=np.int32), np.full(R, 4, np.int32)
+    toks, lps = engine.sample(torch.from_numpy(logits).cuda(), dev_i32(uid), dev_i32(step), temp, 3)
+    want_t, want_lp = osm.sample(logits, uid, step, temp, 3)
+    np.testing.assert_array_equal(toks.cpu().numpy(), want_t)
+    np.testing.assert_allclose(lps.cpu().numpy(), want_lp, atol=LP_ATOL, rtol=LP_RTOL)
+
+
 @pytest.mark.parametrize("V", [5000, 8195])
 @pytest.mark.parametrize("temp,big,rest,small", [
     (1e-36, 400.0, 2.0, 1.0),   # the quotient of one logit overflows
