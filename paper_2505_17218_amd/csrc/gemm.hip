@@ -1,15 +1,23 @@
 // Projection GEMMs C = A[M,K] . W[N,K]^T (fp32 accumulation).
 //
-// bfloat16: v_mfma_f32_32x32x16_bf16 tiles (on gfx950 this MFMA sustains about
-// twice the rate of 16x16x32: measured ~2.1 vs ~1.24 PFLOP/s with register-only
-// operands).  A workgroup of WGM x WGN waves owns a BM x BN output tile; K
-// advances in steps of 64 through a double-buffered LDS tile (row-major, rows
-// padded to 72 elements so fragment reads of 16 consecutive rows hit distinct
-// banks).  Operands are fetched with raw buffer loads (rows outside the operand
-// read as zeros, no branches), PD k-steps ahead of the multiply.  Work items
-// (split, m-tile, n-tile) are enumerated m-fastest and dealt to XCDs in
-// contiguous runs, so blocks that share a weight tile run on the same XCD and
-// reuse it from that XCD's L2.
+// bfloat16: v_mfma_f32_32x32x16_bf16 tiles, K in steps of 64, work items dealt to XCDs in
+// contiguous runs so that blocks that share a weight tile reuse it from one L2.  Rows outside an
+// operand read as zeros (buffer loads past their range), without branches.  Every kernel
+// accumulates an output element with the same chain of MFMAs over k, so the choice of kernel and
+// tile, which follows the sizes (launch_gemm, launch_gemm_qkv_rope), changes no bit.  They
+// differ in how the operands travel and in what then bounds them:
+//   gemm_stream_k         batches of a few row blocks (up to 64-256 rows): narrow tiles, up to
+//                         eight steps of both operands on their way into LDS; latency, weights
+//   gemm_lds_k            one to two rounds of 64 x 64 .. 128 x 128 tiles (the output projection
+//                         and the fused QKV projection at 256-4096 rows, the split down
+//                         projection at 385-640): direct to LDS, a ring of stages
+//   gemm_wide_k           large batches: 256 x 256 .. 128 x 128 tiles, direct to LDS, fragments
+//                         double-buffered in registers; the matrix pipes and the power limit
+//   gemm_wide_persist_k   the same from two rounds of 256 x 256 tiles on, in work-groups that stay
+//   gemm_bf16_k           register-staged, where none of these is faster: gate/up at 129-384 rows
+//                         and its last columns beside a launch of whole rounds, the LM head at
+//                         65-256 rows, and what lies between the other kernels' ranges in the
+//                         down, fused QKV and widest unsplit projections
 //
 // float32: a plain LDS-tiled VALU kernel (the fp32 shapes are tiny correctness
 // configurations).
@@ -293,9 +301,11 @@ DASH_DEV void qkv_epilogue(const f32x16_t* acc, float* Cs, const QkvRopeArgs& qa
     }
 }
 
-// On gfx950 the 32x32x16 bf16 MFMA sustains about twice the rate of 16x16x32
-// (measured: ~2.1 vs ~1.24 PFLOP/s with register-only operands), so the main
-// kernel uses 32 x 32 output blocks.  Operand layout (per 16-wide k-step): lane l
+// The register-staged kernel: a workgroup of WGM x WGN waves owns a BM x BN output tile; a step
+// goes through registers into a double-buffered LDS tile, its loads PD steps ahead of the
+// multiply.  On gfx950 the 32x32x16 bf16 MFMA sustains about twice the rate of 16x16x32
+// (measured: ~2.1 vs ~1.24 PFLOP/s with register-only operands), so every kernel
+// here uses 32 x 32 output blocks.  Operand layout (per 16-wide k-step): lane l
 // holds row (l % 32) and k (l / 32) * 8 .. +8; output register i of lane l is
 // row (i / 4) * 8 + (l / 32) * 4 + i % 4, column l % 32.
 // LDS tiles are row-major with rows padded to 72 elements (fragment reads of 16
@@ -467,7 +477,8 @@ gemm_bf16_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __
 // identical results.  Measured on the 1.5B decode shapes at 1024 rows (weights cold):
 // the output projection 14.7 -> 10.6 us, the QKV projection 15.5 -> 11.5 us with
 // 128 x 64 tiles; gate/up, down and the LM head gain nothing (their per-CU rate stays
-// at ~30% of the MFMA peak either way), so they keep gemm_bf16_k.
+// at ~30% of the MFMA peak either way: a step's fragments are read right before the MFMAs that
+// use them); their large batches run on gemm_wide_k, which reads them a slice ahead.
 template <int BM, int BN, int WGM, int WGN, int S, int EPI, int WPOL = 0>
 __global__ void __launch_bounds__(64 * WGM * WGN)
 gemm_lds_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __restrict__ C, int M, int N, int K,
@@ -669,7 +680,9 @@ DASH_DEV void wide_qkv_rows(const QkvRopeArgs& qa, int M, int m0, int tid, WideQ
 // column blocks two (head dim 128) or one (64) apart.  Rotated q and k leave through LDS of
 // the wave's own (hs: 32 rows of kQkvRow elements), 16 bytes a lane: q rows are contiguous,
 // and so are 8 dims of a key in the K block.  (With 2-byte stores per element the 1.5B
-// projection of 16,384 rows took 117 us instead of 90.)
+// projection of 16,384 rows took 117 us instead of 90.)  The appends are plain stores: as
+// non-temporal ones, as in qkv_epilogue, a decode step of 2048 rows (3B) took the same time
+// (its attention, which reads them next, 149.9-150.6 against 150.1 us).
 constexpr int kQkvRow = 128 + 8;
 
 template <int BM, int WM, int TM>
@@ -1316,8 +1329,8 @@ hipError_t run_wide_sum(const void* A, const void* W, void* C, int M, int N, int
 // Column blocks: TN consecutive ones (fp32 store), or gate columns then the up columns of the
 // same h columns (SwiGLU).  (With the QKV projection's RoPE and KV append in the epilogue the
 // one launch took 7.7-12 us at 16-64 rows against 7.6-10.4 for this kernel and the append
-// kernel: few waves chase the page look-ups and scattered stores; not kept.)  Measured (weights cold, against the register-staged 64 x 32 .. 64 x 256 tiles it replaced):
-// QKV / O at 16 rows 0.5B 5.8 -> 4.4 us, 1.5B 7.7 -> 5.5, 3B 9.3 -> 6.6; down 5.4 -> 4.6,
+// kernel: few waves chase the page look-ups and scattered stores; not kept.)  Measured (weights
+// cold, against the register-staged 64 x 32 .. 64 x 256 tiles it replaced): QKV / O at 16 rows 0.5B 5.8 -> 4.4 us, 1.5B 7.7 -> 5.5, 3B 9.3 -> 6.6; down 5.4 -> 4.6,
 // 8.9 -> 7.1, 12.5 -> 10.5; gate/up 9.0 -> 6.7, 14.3 -> 12.5, 21.7 -> 20.6; LM head (weights
 // at 5.9 TB/s) 59 -> 47, 93 -> 78, 132 -> 106.  Same fragments and MFMA order: same bits.
 template <int WM_, int WN_, int TN, int U, int S, int EPI, int WPOL>
@@ -1740,10 +1753,11 @@ hipError_t launch_gemm(int dtype, int epi, const void* A, const void* W, void* C
                     // Whole rounds of 256x256 tiles leave a last round under half full: those
                     // rounds run as one launch over the columns they cover, the remaining
                     // columns as a second launch on the largest of 128x256, 128x128 and 64x128
-                    // tiles that still gives it 128 or more work-groups (else 64x128).  Measured
-                    // with dash_gemm_bench at 1024 and 2048 rows: 1.5B 70.9 -> 63.0 us and
-                    // 132.1 -> 114.5 us, 3B at 1024 rows 108.7 -> 96.9 us, 0.5B at 2048 rows
-                    // 44.9 -> 43.0 us (a last round at least half full runs whole, as below).
+                    // tiles that still gives it 128 or more work-groups (else 64x128).
+                    // us (dash_gemm_bench, weights cold), two launches / one of 256x256 / the
+                    // best other tile in one: 1.5B at 1024 rows 58 / 71 / 69 and at 2048 104 /
+                    // 117 / 113, 3B at 1024 91-93 / 105 / 90, 0.5B at 2048 40 / 50 / 43 (a
+                    // last round at least half full runs whole, as below).
                     const int c_split = (int)split_tiles * 128;
                     hipError_t e = run_wide_cols<2, 4, 4, 2, EPI_SWIGLU>(A, W, C, M, N, K, ldc, 1, 0, 0, c_split, st);
                     if (e != hipSuccess) return e;

@@ -8,13 +8,19 @@
 // variants of a case are timed in interleaved rounds after a common warm-up of about
 // 20 ms, and each reports its median round: timing one variant after another instead
 // made whichever ran first up to 10% slower (clock ramp after the host-side set-up).
+// What the variant before left in the caches stays in a variant's time: the same kernel listed
+// twice differs by up to 5% at the LM head's sizes (hundreds of MB of output), 2% elsewhere.
 //
-//   dash_gemm_bench [reps per round] [small]
+//   dash_gemm_bench [reps per round] [small|split|rows|large]
 //
 // With "small", the decode batches of one 64-row block (16, 32 and 64 rows) instead:
-// the tiles that stream the weights, with two to eight k-steps in flight per thread,
-// and the fused QKV kernel against the projection followed by the RoPE / KV-append
-// kernel of elementwise.hip (the path the decode step takes at these batches).
+// the streaming kernel against register-staged tiles with two to eight k-steps in flight
+// per thread, and the fused QKV kernel against the projection followed by the RoPE /
+// KV-append kernel of elementwise.hip (the path the decode step takes at these batches).
+// With "split", gate/up and the 1.5B LM head by column ranges; with "rows", the LM heads and
+// one-round gate/up projections at two to eight row tiles; with "large", prefill sizes:
+// the wide tiles, one work-group per tile and in work-groups that stay, against the
+// register-staged ones, and the down projection's partials left and summed.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -203,9 +209,44 @@ struct QkvCase {
     }
 };
 
+// The wide 256x256 tile with a work-group per tile, whatever the number of rounds.
+template <int EPI>
+hipError_t wide_once(const void* A, const void* W, void* C, int M, int N, int K, int ldc, int ns, size_t ss,
+                     hipStream_t st) {
+    constexpr int tn = EPI == EPI_SWIGLU ? 128 : 256;
+    const int m_tiles = (M + 255) / 256, n_tiles = ((EPI == EPI_SWIGLU ? N / 2 : N) + tn - 1) / tn;
+    const int kps = ((K + ns - 1) / ns + kBK - 1) / kBK * kBK;
+    if ((K + kps - 1) / kps != ns || K % kBK) return hipErrorInvalidValue;
+    const int gm = n_tiles >= 16 ? 6 : 4;
+    if (EPI == EPI_STORE_F32 && (size_t)M * N * ns * 4 > ((size_t)256 << 20))  // streaming stores, as in production
+        gemm_wide_k<2, 4, 4, 2, EPI_STORE_F32, 2, true><<<m_tiles * n_tiles * ns, 512, 0, st>>>(
+            (const bf16_t*)A, (const bf16_t*)W, C, M, N, K, ldc, m_tiles, n_tiles, 0, gm, kps, ss, QkvRopeArgs{});
+    else
+        gemm_wide_k<2, 4, 4, 2, EPI, 2, false><<<m_tiles * n_tiles * ns, 512, 0, st>>>(
+            (const bf16_t*)A, (const bf16_t*)W, C, M, N, K, ldc, m_tiles, n_tiles, 0, gm, kps, ss, QkvRopeArgs{});
+    return hipGetLastError();
+}
+
+// The same tile in work-groups that stay, whatever the number of rounds (unsplit; the caller's
+// sizes allow 16-byte output runs).
+template <int EPI>
+hipError_t wide_stay(const void* A, const void* W, void* C, int M, int N, int K, int ldc, hipStream_t st) {
+    constexpr int tn = EPI == EPI_SWIGLU ? 128 : 256;
+    const int m_tiles = (M + 255) / 256, n_tiles = ((EPI == EPI_SWIGLU ? N / 2 : N) + tn - 1) / tn;
+    if (K % kBK || N % 16) return hipErrorInvalidValue;
+    const int gm = n_tiles >= 16 ? 6 : 4, tiles = m_tiles * n_tiles;
+    if (EPI == EPI_STORE_F32 && (size_t)M * N * 4 > ((size_t)256 << 20))
+        gemm_wide_persist_k<EPI_STORE_F32, true><<<256, 512, 0, st>>>((const bf16_t*)A, (const bf16_t*)W, C, M, N, K, ldc,
+                                                                      m_tiles, n_tiles, 0, gm, K, 0, tiles);
+    else
+        gemm_wide_persist_k<EPI, false><<<256, 512, 0, st>>>((const bf16_t*)A, (const bf16_t*)W, C, M, N, K, ldc, m_tiles,
+                                                             n_tiles, 0, gm, K, 0, tiles);
+    return hipGetLastError();
+}
+
 // Batches of one 64-row block: the projections stream their weights (every weight byte
-// read by one work-group) and each work-group's k-loop is a chain of dependent loads,
-// so the variants differ in how many k-steps each thread keeps in flight.
+// read by one work-group) and each work-group's k-loop is a chain of dependent loads;
+// the register-staged variants differ in how many k-steps each thread keeps in flight.
 void bench_small(const ModelShape* shapes, int n_shapes, int reps, hipStream_t st, std::mt19937& rng) {
     constexpr int W = 2;  // non-temporal weight loads
     char label[128];
@@ -230,6 +271,7 @@ void bench_small(const ModelShape* shapes, int n_shapes, int reps, hipStream_t s
                 auto out = [&](bool ref) { return ref ? c0.p : c1.p; };
                 const std::vector<Variant> vs = {
                     {"production", [&](const void* wp, bool r) { return launch_gemm(1, EPI_STORE_F32, a.p, wp, out(r), M, N, K, N, ns, ss, st); }},
+                    {"64x32pd4", [&](const void* wp, bool r) { return run_bf16<64, 32, 2, 1, 4, EPI_STORE_F32, W>(a.p, wp, out(r), M, N, K, N, ns, ss, st); }},
                     {"pd2", [&](const void* wp, bool r) { return run_bf16<64, 32, 2, 1, 2, EPI_STORE_F32, W>(a.p, wp, out(r), M, N, K, N, ns, ss, st); }},
                     {"pd6", [&](const void* wp, bool r) { return run_bf16<64, 32, 2, 1, 6, EPI_STORE_F32, W>(a.p, wp, out(r), M, N, K, N, ns, ss, st); }},
                     {"pd8", [&](const void* wp, bool r) { return run_bf16<64, 32, 2, 1, 8, EPI_STORE_F32, W>(a.p, wp, out(r), M, N, K, N, ns, ss, st); }},
@@ -250,6 +292,7 @@ void bench_small(const ModelShape* shapes, int n_shapes, int reps, hipStream_t s
                 const std::vector<Variant> vs = {
                     {"production", [&](const void* wp, bool r) { return launch_gemm(1, EPI_SWIGLU, a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
                     {"64x128pd2", [&](const void* wp, bool r) { return run_bf16<64, 128, 2, 2, 2, EPI_SWIGLU, W>(a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
+                    {"64x128pd3", [&](const void* wp, bool r) { return run_bf16<64, 128, 2, 2, 3, EPI_SWIGLU, W>(a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
                     {"64x128pd4", [&](const void* wp, bool r) { return run_bf16<64, 128, 2, 2, 4, EPI_SWIGLU, W>(a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
                     {"64x128pd6", [&](const void* wp, bool r) { return run_bf16<64, 128, 2, 2, 6, EPI_SWIGLU, W>(a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
                     {"64x64pd2", [&](const void* wp, bool r) { return run_bf16<64, 64, 2, 1, 2, EPI_SWIGLU, W>(a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
@@ -359,6 +402,115 @@ void bench_gu_split(const ModelShape* shapes, int n_shapes, int reps, hipStream_
     }
 }
 
+// Prefill sizes: one chunk of 64 prompts of 256 tokens, and a ragged one.
+void bench_large(const ModelShape* shapes, int n_shapes, int reps, hipStream_t st, std::mt19937& rng) {
+    char label[160];
+    for (int si = 0; si < n_shapes; ++si) {
+        const ModelShape& sh = shapes[si];
+        for (int M : {4206, 16384}) {
+            {
+                const int ff = sh.ff, N = 2 * ff, K = sh.d;
+                Weights w(N, K, rng);
+                Dev a((size_t)M * K * 2), c0((size_t)M * ff * 2), c1((size_t)M * ff * 2);
+                const auto ha = randn_bf16((size_t)M * K, 1.f, rng);
+                CK(hipMemcpy(a.p, ha.data(), ha.size() * 2, hipMemcpyHostToDevice));
+                auto out = [&](bool ref) { return ref ? c0.p : c1.p; };
+                const std::vector<Variant> vs = {
+                    {"production", [&](const void* wp, bool r) { return launch_gemm(1, EPI_SWIGLU, a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
+                    {"wide_once", [&](const void* wp, bool r) { return wide_once<EPI_SWIGLU>(a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
+                    {"256x256w16", [&](const void* wp, bool r) { return run_bf16<256, 256, 4, 4, 2, EPI_SWIGLU>(a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
+                };
+                snprintf(label, sizeof label, "%-5s gu   M=%5d N=%5d K=%5d     ", sh.name, M, N, K);
+                bench_case(label, vs, w, reps, st, [&] { CK(hipMemset(c1.p, 0xFF, c1.n)); },
+                           [&] { return same_bytes(c0, c1); });
+            }
+            {
+                const int N = sh.d, K = sh.ff, ns = gemm_pick_splits(1, EPI_STORE_F32, N, K);
+                Weights w(N, K, rng);
+                const size_t ss = (size_t)M * N, cn = ns * ss;
+                Dev a((size_t)M * K * 2), c0(cn * 4), c1(cn * 4);
+                const auto ha = randn_bf16((size_t)M * K, 1.f, rng);
+                CK(hipMemcpy(a.p, ha.data(), ha.size() * 2, hipMemcpyHostToDevice));
+                auto out = [&](bool ref) { return ref ? c0.p : c1.p; };
+                const std::vector<Variant> parts = {
+                    {"partials", [&](const void* wp, bool r) { return launch_gemm(1, EPI_STORE_F32, a.p, wp, out(r), M, N, K, N, ns, ss, st); }},
+                    {"wide_once", [&](const void* wp, bool r) { return wide_once<EPI_STORE_F32>(a.p, wp, out(r), M, N, K, N, ns, ss, st); }},
+                    {"256x256w16", [&](const void* wp, bool r) { return run_bf16<256, 256, 4, 4, 2, EPI_STORE_F32>(a.p, wp, out(r), M, N, K, N, ns, ss, st); }},
+                };
+                snprintf(label, sizeof label, "%-5s down M=%5d N=%5d K=%5d s%d  ", sh.name, M, N, K, ns);
+                bench_case(label, parts, w, reps, st, [&] { CK(hipMemset(c1.p, 0xFF, c1.n)); },
+                           [&] { return same_bytes(c0, c1); });
+                CK(hipMemset(c0.p, 0, c0.n));
+                const std::vector<Variant> sums = {
+                    {gemm_sum_pays(1, M, N, K, ns) ? "summed (production)" : "summed",
+                     [&](const void* wp, bool r) { return launch_gemm_sum(a.p, wp, out(r), M, N, K, ns, st); }},
+                    {"256x128", [&](const void* wp, bool r) { return run_wide_sum<4, 2, 2, 2, 3>(a.p, wp, out(r), M, N, K, ns, st); }},
+                    {"128x256", [&](const void* wp, bool r) { return run_wide_sum<2, 4, 2, 2, 3>(a.p, wp, out(r), M, N, K, ns, st); }},
+                };
+                bench_case(label, sums, w, reps, st, [&] { CK(hipMemset(c1.p, 0, c1.n)); },
+                           [&] { return same_bytes(c0, c1); });
+            }
+            if (gemm_qkv_fusable(1, sh.n_heads, sh.n_kv, sh.hd)) {
+                QkvCase c(sh, M, rng);
+                const void* A = c.a.p;
+                const int N = c.N, K = c.K;
+                const std::vector<Variant> vs = {
+                    {"production", [&](const void* wp, bool r) { return launch_gemm_qkv_rope(A, wp, M, N, K, c.args(r), st); }},
+                    {"wide256x256", [&](const void* wp, bool r) { return run_wide<4, 2, 2, 4, EPI_QKV_ROPE>(A, wp, nullptr, M, N, K, 0, 1, 0, st, c.args(r)); }},
+                    {"wide128x128", [&](const void* wp, bool r) { return run_wide<4, 1, 1, 4, EPI_QKV_ROPE>(A, wp, nullptr, M, N, K, 0, 1, 0, st, c.args(r)); }},
+                    {"64x128", [&](const void* wp, bool r) { return run_bf16<64, 128, 2, 4, 2, EPI_QKV_ROPE>(A, wp, nullptr, M, N, K, 0, 1, 0, st, c.args(r)); }},
+                };
+                snprintf(label, sizeof label, "%-5s qkv  M=%5d N=%5d K=%5d     ", sh.name, M, N, K);
+                c.run(label, vs, reps, st);
+            }
+        }
+    }
+}
+
+// Two to eight row tiles: the LM head in work-groups that stay or of one tile, and gate/up
+// where one round of 256x256 tiles holds it.
+void bench_rows(const ModelShape* shapes, int n_shapes, int reps, hipStream_t st, std::mt19937& rng) {
+    char label[160];
+    for (int si = 0; si < n_shapes; ++si) {
+        const ModelShape& sh = shapes[si];
+        for (int M : {300, 419, 512, 640, 768, 1024, 1280, 1536, 2048}) {
+            {
+                const int N = 151936, K = sh.d;
+                Weights w(N, K, rng);
+                Dev a((size_t)M * K * 2), c0((size_t)M * N * 4), c1((size_t)M * N * 4);
+                const auto ha = randn_bf16((size_t)M * K, 1.f, rng);
+                CK(hipMemcpy(a.p, ha.data(), ha.size() * 2, hipMemcpyHostToDevice));
+                auto out = [&](bool ref) { return ref ? c0.p : c1.p; };
+                const std::vector<Variant> vs = {
+                    {"production", [&](const void* wp, bool r) { return launch_gemm(1, EPI_STORE_F32, a.p, wp, out(r), M, N, K, N, 1, 0, st); }},
+                    {"wide_once", [&](const void* wp, bool r) { return wide_once<EPI_STORE_F32>(a.p, wp, out(r), M, N, K, N, 1, 0, st); }},
+                    {"wide_stay", [&](const void* wp, bool r) { return wide_stay<EPI_STORE_F32>(a.p, wp, out(r), M, N, K, N, st); }},
+                    {"256x256w16", [&](const void* wp, bool r) { return run_bf16<256, 256, 4, 4, 2, EPI_STORE_F32>(a.p, wp, out(r), M, N, K, N, 1, 0, st); }},
+                };
+                snprintf(label, sizeof label, "%-5s lm   M=%5d N=%6d K=%5d     ", sh.name, M, N, K);
+                bench_case(label, vs, w, std::max(4, reps / 3), st, [&] { CK(hipMemset(c1.p, 0xFF, c1.n)); },
+                           [&] { return same_bytes(c0, c1); });
+            }
+            const int ff = sh.ff, N = 2 * ff, K = sh.d;
+            if ((M + 255) / 256 * ((ff + 127) / 128) > 256) continue;
+            Weights w(N, K, rng);
+            Dev a((size_t)M * K * 2), c0((size_t)M * ff * 2), c1((size_t)M * ff * 2);
+            const auto ha = randn_bf16((size_t)M * K, 1.f, rng);
+            CK(hipMemcpy(a.p, ha.data(), ha.size() * 2, hipMemcpyHostToDevice));
+            auto out = [&](bool ref) { return ref ? c0.p : c1.p; };
+            const std::vector<Variant> vs = {
+                {"production", [&](const void* wp, bool r) { return launch_gemm(1, EPI_SWIGLU, a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
+                {"wide256x256", [&](const void* wp, bool r) { return wide_once<EPI_SWIGLU>(a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
+                {"wide256x128s3", [&](const void* wp, bool r) { return run_wide<4, 2, 2, 2, EPI_SWIGLU, 3>(a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
+                {"256x256w16", [&](const void* wp, bool r) { return run_bf16<256, 256, 4, 4, 2, EPI_SWIGLU>(a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
+            };
+            snprintf(label, sizeof label, "%-5s gu   M=%5d N=%6d K=%5d     ", sh.name, M, N, K);
+            bench_case(label, vs, w, reps, st, [&] { CK(hipMemset(c1.p, 0xFF, c1.n)); },
+                       [&] { return same_bytes(c0, c1); });
+        }
+    }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -372,6 +524,24 @@ int main(int argc, char** argv) {
         printf("kernel timings in us at 16-64 rows (weights cold, median of interleaved rounds); alternatives "
                "marked = give the production bits\n");
         bench_small(shapes, 3, reps, st, rng);
+        return 0;
+    }
+    if (argc > 2 && strcmp(argv[2], "large") == 0) {
+        hipStream_t st;
+        CK(hipStreamCreate(&st));
+        std::mt19937 rng(7);
+        printf("kernel timings in us at prefill sizes (weights cold, median of interleaved rounds); alternatives "
+               "marked = give the production bits\n");
+        bench_large(shapes, 3, reps, st, rng);
+        return 0;
+    }
+    if (argc > 2 && strcmp(argv[2], "rows") == 0) {
+        hipStream_t st;
+        CK(hipStreamCreate(&st));
+        std::mt19937 rng(7);
+        printf("kernel timings in us at two to eight row tiles (weights cold, median of interleaved rounds); "
+               "alternatives marked = give the production bits\n");
+        bench_rows(shapes, 3, reps, st, rng);
         return 0;
     }
     if (argc > 2 && strcmp(argv[2], "split") == 0) {
@@ -406,6 +576,7 @@ int main(int argc, char** argv) {
                     {"lds64x64", [&](const void* wp, bool r) { return run_lds<64, 64, 2, 2, 4, EPI_STORE_F32>(a.p, wp, out(r), M, N, K, N, 1, 0, st); }},
                     {"lds64x128", [&](const void* wp, bool r) { return run_lds<64, 128, 2, 2, 4, EPI_STORE_F32>(a.p, wp, out(r), M, N, K, N, 1, 0, st); }},
                     {"lds128x128", [&](const void* wp, bool r) { return run_lds<128, 128, 2, 2, 4, EPI_STORE_F32>(a.p, wp, out(r), M, N, K, N, 1, 0, st); }},
+                    {"wide128x128s4", [&](const void* wp, bool r) { return run_wide<4, 2, 1, 2, EPI_STORE_F32, 4>(a.p, wp, out(r), M, N, K, N, 1, 0, st); }},
                 };
                 snprintf(label, sizeof label, "%-5s o    M=%4d N=%5d K=%5d     ", sh.name, M, N, K);
                 bench_case(label, vs, w, reps, st, [&] { CK(hipMemset(c1.p, 0xFF, c1.n)); },
@@ -427,6 +598,9 @@ int main(int argc, char** argv) {
                     {"128x256w16", [&](const void* wp, bool r) { return run_bf16<128, 256, 4, 4, 2, EPI_SWIGLU>(a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
                     {"256x256w16", [&](const void* wp, bool r) { return run_bf16<256, 256, 4, 4, 2, EPI_SWIGLU>(a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
                     {"256x256w8", [&](const void* wp, bool r) { return run_bf16<256, 256, 4, 2, 2, EPI_SWIGLU>(a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
+                    {"wide256x256", [&](const void* wp, bool r) { return run_wide<2, 4, 4, 2, EPI_SWIGLU>(a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
+                    {"wide256x128s3", [&](const void* wp, bool r) { return run_wide<4, 2, 2, 2, EPI_SWIGLU, 3>(a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
+                    {"wide128x128", [&](const void* wp, bool r) { return run_wide<2, 2, 2, 2, EPI_SWIGLU>(a.p, wp, out(r), M, N, K, ff, 1, 0, st); }},
                 };
                 snprintf(label, sizeof label, "%-5s gu   M=%4d N=%5d K=%5d     ", sh.name, M, N, K);
                 bench_case(label, vs, w, reps, st, [&] { CK(hipMemset(c1.p, 0xFF, c1.n)); },
@@ -450,6 +624,8 @@ int main(int argc, char** argv) {
                     {"256x256w8", [&](const void* wp, bool r) { return run_bf16<256, 256, 4, 2, 2, EPI_STORE_F32>(a.p, wp, out(r), M, N, K, N, ns, ss, st); }},
                     {"256x256w8t", [&](const void* wp, bool r) { return run_bf16<256, 256, 2, 4, 2, EPI_STORE_F32>(a.p, wp, out(r), M, N, K, N, ns, ss, st); }},
                     {"lds128x128", [&](const void* wp, bool r) { return run_lds<128, 128, 2, 2, 4, EPI_STORE_F32>(a.p, wp, out(r), M, N, K, N, ns, ss, st); }},
+                    {"wide256x256", [&](const void* wp, bool r) { return run_wide<2, 4, 4, 2, EPI_STORE_F32>(a.p, wp, out(r), M, N, K, N, ns, ss, st); }},
+                    {"wide256x128s3", [&](const void* wp, bool r) { return run_wide<4, 2, 2, 2, EPI_STORE_F32, 3>(a.p, wp, out(r), M, N, K, N, ns, ss, st); }},
                 };
                 snprintf(label, sizeof label, "%-5s down M=%4d N=%5d K=%5d s%d  ", sh.name, M, N, K, ns);
                 bench_case(label, vs, w, reps, st, [&] { CK(hipMemset(c1.p, 0xFF, c1.n)); },
@@ -471,6 +647,7 @@ int main(int argc, char** argv) {
                     {"128x256w16", [&](const void* wp, bool r) { return run_bf16<128, 256, 4, 4, 2, EPI_STORE_F32>(a.p, wp, out(r), M, N, K, N, 1, 0, st); }},
                     {"256x128w8", [&](const void* wp, bool r) { return run_bf16<256, 128, 4, 2, 2, EPI_STORE_F32>(a.p, wp, out(r), M, N, K, N, 1, 0, st); }},
                     {"lds128x128", [&](const void* wp, bool r) { return run_lds<128, 128, 2, 2, 4, EPI_STORE_F32>(a.p, wp, out(r), M, N, K, N, 1, 0, st); }},
+                    {"wide_once", [&](const void* wp, bool r) { return wide_once<EPI_STORE_F32>(a.p, wp, out(r), M, N, K, N, 1, 0, st); }},
                 };
                 snprintf(label, sizeof label, "%-5s lm   M=%4d N=%6d K=%4d    ", sh.name, M, N, K);
                 bench_case(label, vs, w, std::max(2, reps / 8), st, [&] { CK(hipMemset(c1.p, 0xFF, c1.n)); },
@@ -492,6 +669,8 @@ int main(int argc, char** argv) {
                     {"lds64x128s3", [&](const void* wp, bool r) { return run_lds<64, 128, 2, 2, 3, EPI_QKV_ROPE>(A, wp, nullptr, M, N, K, 0, 1, 0, st, args(r)); }},
                     {"64x128pd3", [&](const void* wp, bool r) { return run_bf16<64, 128, 2, 4, 3, EPI_QKV_ROPE>(A, wp, nullptr, M, N, K, 0, 1, 0, st, args(r)); }},
                     {"64x128pd4", [&](const void* wp, bool r) { return run_bf16<64, 128, 2, 4, 4, EPI_QKV_ROPE>(A, wp, nullptr, M, N, K, 0, 1, 0, st, args(r)); }},
+                    {"wide256x256", [&](const void* wp, bool r) { return run_wide<4, 2, 2, 4, EPI_QKV_ROPE>(A, wp, nullptr, M, N, K, 0, 1, 0, st, args(r)); }},
+                    {"wide128x128", [&](const void* wp, bool r) { return run_wide<4, 1, 1, 4, EPI_QKV_ROPE>(A, wp, nullptr, M, N, K, 0, 1, 0, st, args(r)); }},
                     {"64x128w4pd3", [&](const void* wp, bool r) { return run_bf16<64, 128, 2, 2, 3, EPI_QKV_ROPE>(A, wp, nullptr, M, N, K, 0, 1, 0, st, args(r)); }},
                 };
                 snprintf(label, sizeof label, "%-5s qkv  M=%4d N=%5d K=%5d     ", sh.name, M, N, K);
