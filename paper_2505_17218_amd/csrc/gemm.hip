@@ -625,9 +625,10 @@ gemm_lds_k(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, void* __r
 // Eight waves of 128 x 64 on a 256 x 256 tile: each fragment feeds four (two) MFMAs, so LDS
 // reads take ~770 cycles of the 2060 MFMA cycles of a step; two waves per SIMD fill each
 // other's barrier waits (four waves of 128 x 128, one per SIMD, 1-8% slower; sixteen waves
-// of 64 x 64 with register-staged operands, the earlier kernel, 10-20% slower).  At 4096 x
-// 4096 x 12288 it runs at 1353 TFLOP/s with the MFMA pipes 73% busy and the clock down to
-// 1.8 GHz: the power limit, not the pipe, is next.  What a shape loses beyond that is per
+// of 64 x 64 with register-staged operands, the earlier kernel, 10-20% slower).  Gate/up
+// of the 1.5B shape at 16,384 rows (in work-groups that stay) runs at 1294 TFLOP/s with the MFMA
+// pipes 71% busy and the clock down to 1.73 GHz (MFMA counters): the power limit, not the pipe,
+// is next.  What a shape loses beyond that is per
 // tile (load latency before the first step, the output after the last).  Stages of 32-deep
 // half lines (four or five of them in flight) were 5-10% slower, and touching the lines of
 // later steps (one dword per 64 bytes) 6-12%: the vector memory path, 64 bytes a cycle
